@@ -1,0 +1,319 @@
+"""Performance cases: the calls a program makes of the relaxed online convolution library.
+
+Every case goes through the Python binding ``paper_2410_12982_amd.lcsm`` (the C ABI's names) and is one of
+
+* ``graph``  a generation of all L positions recorded once (``Lcsm.capture``) and replayed, inputs handed in
+             (``chain`` false) or produced by the built-in closed loop (``chain`` true);
+* ``steps``  the same generation by one ``Lcsm.step`` call per position;
+* ``serve``  ``Lcsm.prefill`` of a prompt of P positions, then n single steps;
+* ``dd``     data-dependent filters: ``Dd.step`` for every position, recorded as HIP graphs and replayed;
+* ``synth``  the synthetic end-to-end model: ``Synth.step`` for n positions, recorded and replayed.
+
+All data is fp32.  M layers, B batch rows, D channels, L positions.
+"""
+from __future__ import annotations
+
+import math
+
+import torch
+
+import paper_2410_12982_amd.lcsm as lcsm
+
+DEVICE = "cuda:0"
+# positions recorded per torch graph (graphs of more than about 16k kernel nodes are avoided)
+SEGMENT = {"dd": 2048, "synth": 64}
+
+
+def listed():
+    return [
+        # one user's small model, a call per position: latency and launches are everything
+        dict(name="steps-small", kind="steps", M=1, B=1, D=16, L=1024, decay=200.0),
+        # one layer at an ordinary width: every step is a launch of a few microseconds
+        dict(name="gen-layer", kind="graph", M=1, B=8, D=768, L=8192, decay=2048.0, chain=False, half=False),
+        # ragged sizes: odd batch, odd channels, a length that is no power of two
+        dict(name="gen-ragged", kind="graph", M=12, B=3, D=515, L=5000, decay=700.0, chain=False, half=False),
+        # an 18-layer model at batch 4: same-size tiles of all layers in one launch
+        dict(name="gen-model", kind="graph", M=18, B=4, D=768, L=32768, decay=2048.0, chain=False, half=False),
+        # the same model with the memory-saving storage (half the state rows)
+        dict(name="gen-half", kind="graph", M=18, B=4, D=768, L=16384, decay=2048.0, chain=False, half=True),
+        # long context, one sequence: the largest tiles do not fit LDS
+        dict(name="gen-long", kind="graph", M=18, B=1, D=1024, L=65536, decay=16384.0, chain=False, half=False),
+        # wide batch: half a million columns, bound by memory from the first step on
+        dict(name="gen-wide", kind="graph", M=16, B=16, D=2048, L=4096, decay=2048.0, chain=False, half=False),
+        # the closed loop: every input comes from the previous layer's or position's output
+        dict(name="loop-model", kind="graph", M=18, B=4, D=768, L=1024, decay=200.0, chain=True, half=False),
+        # serving: a known prompt, then token by token
+        dict(name="serve-model", kind="serve", M=18, B=4, D=768, L=16384, decay=2048.0, P=8192, n=256),
+        # filters that depend on the data, wide batch
+        dict(name="dd-wide", kind="dd", M=16, B=16, D=2048, L=2048, decay=256.0),
+        # the whole model with its MLP blocks, at batch 4 and at batch 16
+        dict(name="synth-model", kind="synth", M=18, B=4, D=768, L=4096, decay=512.0, n=128),
+        dict(name="synth-wide", kind="synth", M=32, B=16, D=2048, L=512, decay=128.0, n=32),
+    ]
+
+
+def _log_int(rng, lo, hi, step=1):
+    v = int(round(math.exp(rng.uniform(math.log(lo), math.log(hi + 1)))))
+    return max(lo, min(hi, v // step * step))
+
+
+def draw(rng):
+    kind = rng.choice(["graph", "graph", "graph", "chain", "steps", "serve", "dd", "synth"])
+    if kind in ("graph", "dd"):
+        while True:
+            M, B = _log_int(rng, 1, 32), rng.choice([1, 1, 2, 3, 4, 6, 8, 16])
+            D = _log_int(rng, 16, 2048, rng.choice([1, 1, 16, 64]))
+            L = _log_int(rng, 256, 32768 if kind == "graph" else 4096)
+            cells = M * B * D * L
+            if cells <= (1.2e9 if kind == "graph" else 9e8):
+                break
+        c = dict(kind=kind, M=M, B=B, D=D, L=L, decay=max(16.0, L / 8.0))
+        if kind == "graph":
+            c.update(chain=False, half=rng.random() < 0.2)
+        return c
+    if kind == "chain":
+        while True:
+            M, B, D = _log_int(rng, 1, 24), rng.choice([1, 2, 3, 4, 8]), _log_int(rng, 16, 1024)
+            if M * B * D <= 60000:
+                break
+        return dict(kind="graph", M=M, B=B, D=D, L=_log_int(rng, 128, 1024), decay=float(_log_int(rng, 32, 200)),
+                    chain=True, half=False)
+    if kind == "steps":
+        return dict(kind=kind, M=_log_int(rng, 1, 8), B=rng.choice([1, 1, 2, 4]), D=_log_int(rng, 16, 512),
+                    L=_log_int(rng, 128, 1024), decay=float(_log_int(rng, 32, 256)))
+    if kind == "serve":
+        while True:
+            M, B, D = _log_int(rng, 1, 18), rng.choice([1, 1, 2, 4, 8]), _log_int(rng, 16, 1024, rng.choice([1, 16]))
+            P, n = 1 << rng.randint(6, 13), _log_int(rng, 16, 256)
+            L = max(2 * P, P + n) + rng.choice([0, 0, _log_int(rng, 1, 1000)])
+            if M * B * D * L <= 9e8:
+                break
+        return dict(kind=kind, M=M, B=B, D=D, L=L, decay=max(16.0, L / 8.0), P=P, n=n)
+    while True:
+        M, B, D = _log_int(rng, 1, 32), rng.randint(1, 16), _log_int(rng, 64, 2048, rng.choice([4, 64]))
+        if M * D * D <= 32 * 2048 * 2048:
+            break
+    return dict(kind="synth", M=M, B=B, D=D, L=512, decay=128.0, n=_log_int(rng, 8, 32))
+
+
+# ---------------------------------------------------------------- inputs
+
+def _gen(seed, stream):
+    g = torch.Generator(device=DEVICE)
+    g.manual_seed(int(seed) * 16 + stream)
+    return g
+
+
+def _filters(case, seed):
+    """h[m, d, k] = N(0, 1) exp(-k/decay); in the closed loops of unit expected norm, so that a layer does not
+    amplify and the loop's rounding errors stay rounding errors."""
+    M, D, L, decay = case["M"], case["D"], case["L"], case["decay"]
+    h = torch.randn((M, D, L), generator=_gen(seed, 0), device=DEVICE)
+    h *= torch.exp(torch.arange(L, device=DEVICE, dtype=torch.float64) / -decay).float()
+    if case.get("chain"):
+        h *= math.sqrt(2.0 / decay)
+    return h
+
+
+def _slabs(case, seed, n, stream, rows=("M", "B", "D")):
+    """n inputs of one position each, uniform on [-1/2, 1/2)."""
+    shape = (n,) + tuple(case[r] for r in rows)
+    return torch.rand(shape, generator=_gen(seed, stream), device=DEVICE).sub_(0.5)
+
+
+def _rho(case, seed):
+    r = torch.randn((case["L"], case["M"], case["B"], case["D"]), generator=_gen(seed, 2), device=DEVICE)
+    r *= torch.exp(torch.arange(case["L"], device=DEVICE) / -case["decay"]).view(-1, 1, 1, 1)
+    return r
+
+
+def _weights(case, seed):
+    """Weights of the MLP blocks, scaled so that mixer and block together do not amplify."""
+    M, D = case["M"], case["D"]
+    s = 1.0 / (2.0 * math.sqrt(0.5 * case["decay"] + 0.5))
+    w_up = torch.randn((M, 2 * D, D), generator=_gen(seed, 3), device=DEVICE) / math.sqrt(D)
+    b_up = torch.randn((M, 2 * D), generator=_gen(seed, 4), device=DEVICE) * 0.1
+    w_down = torch.randn((M, D, 2 * D), generator=_gen(seed, 5), device=DEVICE) * (s / math.sqrt(2 * D))
+    b_down = torch.randn((M, D), generator=_gen(seed, 6), device=DEVICE) * 0.1
+    return w_up, b_up, w_down, b_down
+
+
+def _noise(case, seed):
+    return torch.randn((case["n"], case["B"], case["D"]), generator=_gen(seed, 7), device=DEVICE) * 0.1
+
+
+def _inputs(case, seed):
+    n = case["P"] + case["n"] if case["kind"] == "serve" else case["L"]
+    y = _slabs(case, seed, n, 1)
+    return y.mul_(0.35) if case.get("chain") else y
+
+
+# ----------------------------------------------------------- prepare, run
+
+def _record(stream, n, seg, step, reset):
+    """Positions 0 .. n-1 as a chain of graphs, the first one starting with the reset."""
+    graphs = []
+    torch.cuda.synchronize()
+    for p0 in range(0, n, seg):
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g, stream=stream):
+            if p0 == 0:
+                reset()
+            for t in range(p0, min(n, p0 + seg)):
+                step(t)
+        graphs.append(g)
+    return graphs
+
+
+def prepare(case, seed):
+    kind, M, B, D, L = case["kind"], case["M"], case["B"], case["D"], case["L"]
+    if kind == "dd":
+        y, rho = _slabs(case, seed, L, 1), _rho(case, seed)
+        z = torch.empty_like(y)
+        stream = torch.cuda.Stream(DEVICE)
+        ctx = lcsm.Dd(M, B, D, L, stream=stream, device=DEVICE)
+        graphs = _record(stream, L, SEGMENT[kind], lambda t: ctx.step(y[t], rho[t], z[t]), ctx.reset)
+        return dict(kind=kind, ctx=ctx, graphs=graphs, y=y, rho=rho, z=z)
+    if kind == "synth":
+        eps = _noise(case, seed)
+        act = torch.empty((case["n"], M, B, D), device=DEVICE)
+        stream = torch.cuda.Stream(DEVICE)
+        ctx = lcsm.Synth(_filters(case, seed), *_weights(case, seed), B, stream=stream)
+        graphs = _record(stream, case["n"], SEGMENT[kind], lambda t: ctx.step(eps[t], act[t]), ctx.reset)
+        return dict(kind=kind, ctx=ctx, graphs=graphs, eps=eps, z=act)
+    y = _inputs(case, seed)
+    z = torch.empty_like(y)
+    if kind == "graph":
+        stream = torch.cuda.Stream(DEVICE)
+        ctx = lcsm.Lcsm(_filters(case, seed), B, options={"half_state": 1} if case["half"] else None, stream=stream)
+        return dict(kind=kind, ctx=ctx, graph=ctx.capture(y, z, n=L, chain=case["chain"]), y=y, z=z)
+    ctx = lcsm.Lcsm(_filters(case, seed), B)
+    return dict(kind=kind, ctx=ctx, y=y, z=z, P=case.get("P", 0))
+
+
+def run(state):
+    kind, ctx, z = state["kind"], state["ctx"], state["z"]
+    if kind in ("dd", "synth"):
+        for g in state["graphs"]:
+            g.replay()
+        return z
+    if kind == "graph":
+        state["graph"].launch()
+        torch.cuda.current_stream(DEVICE).wait_stream(ctx.stream)
+        return z
+    y, P = state["y"], state["P"]
+    ctx.reset()
+    if P:
+        ctx.prefill(y[:P], z[:P])
+    for t in range(P, y.shape[0]):
+        ctx.step(y[t], z[t])
+    return z
+
+
+# ------------------------------------------------- work, tolerance, exact
+
+def _fft_flops(n):
+    return 5.0 * n * math.log2(n)
+
+
+def _tile_flops(U):
+    """A tile of side U of one column: direct, or as half of a 2U-point complex transform pair and product."""
+    return min(2.0 * U * U, _fft_flops(2 * U) + 6.0 * U)
+
+
+def _mixer_flops(n):
+    """One column's n online positions: the red cells and every gray tile between them."""
+    f, U = 2.0 * n, 1
+    while U < n:
+        f += ((n - 1) // U - (n - 1) // (2 * U)) * _tile_flops(U)
+        U *= 2
+    return f
+
+
+def work(case):
+    """Inputs read once, outputs written once; the relaxed algorithm's operations (the online order is part of the
+    path).  In the model every position needs every weight anew: positions depend on each other and the weights
+    exceed the caches."""
+    kind, M, B, D, L = case["kind"], case["M"], case["B"], case["D"], case["L"]
+    cols = M * B * D
+    if kind == "dd":
+        f, U = 4.0 * L, 1
+        while 2 * U < L:  # two products a tile: twice the direct work, or 5/4 transforms of 2U points more
+            f += ((L - 1) // U - 1) * min(4.0 * U * U, 2.5 * _fft_flops(2 * U) + 16.0 * U)
+            U *= 2
+        return {"bytes": 12.0 * cols * L, "flops": cols * f}
+    if kind == "synth":
+        n = case["n"]
+        weights = M * (4.0 * D * D + 3 * D)
+        return {"bytes": 4.0 * n * (weights + cols + B * D),
+                "flops": n * (2.0 * B * weights) + cols * _mixer_flops(n)}
+    if kind == "serve":
+        P, n = case["P"], case["n"]
+        flops = 2 * _tile_flops(P) + _mixer_flops(n)
+        return {"bytes": 8.0 * cols * (P + n) + 4.0 * M * D * min(L, 2 * P), "flops": cols * flops}
+    return {"bytes": 8.0 * cols * L + 4.0 * M * D * L, "flops": cols * _mixer_flops(L)}
+
+
+def tolerance(case):
+    """About four times the distance from `exact` that the fp32 sums show over these ranges: 2e-7 to 3.5e-7 in the
+    mixers, up to 6e-8 in the model, whose outputs hold the fp32 biases."""
+    return {"rel": 3e-7 if case["kind"] == "synth" else 1.4e-6}
+
+
+def _chunks(total, per, budget):
+    step = max(1, int(budget // per))
+    for a in range(0, total, step):
+        yield a, min(total, a + step)
+
+
+def _conv64(y, h):
+    """Causal convolution along axis 0 of y [n, B, D] with h [n, B or 1, D], in 64 bits."""
+    n = y.shape[0]
+    N = 1 << (2 * n - 1).bit_length()
+    yf = torch.fft.rfft(y.permute(1, 2, 0).contiguous().double(), N)
+    hf = torch.fft.rfft(h.permute(1, 2, 0).contiguous().double(), N)
+    return torch.fft.irfft(yf.mul_(hf), N)[..., :n].permute(2, 0, 1)
+
+
+def _conv_all(y, h_of):
+    """_conv64 of every layer of y [n, M, B, D]; h_of(m, d0, d1): the layer's filters [n, B or 1, d1 - d0]."""
+    n, M, B, D = y.shape
+    z = torch.empty(y.shape, dtype=torch.float64, device=y.device)
+    for m in range(M):
+        for d0, d1 in _chunks(D, 64.0 * B * n, 4e9):
+            z[:, m, :, d0:d1] = _conv64(y[:, m, :, d0:d1], h_of(m, d0, d1))
+    return z
+
+
+def exact(case, seed):
+    kind, M, B, D, L = case["kind"], case["M"], case["B"], case["D"], case["L"]
+    if kind == "dd":
+        rho = _rho(case, seed)
+        return _conv_all(_slabs(case, seed, L, 1), lambda m, a, b: rho[:, m, :, a:b])
+    h = _filters(case, seed)
+    if kind == "synth" or case.get("chain"):
+        n = case["n"] if kind == "synth" else L
+        hrev = h[..., :n].permute(2, 0, 1).flip(0).double().contiguous().unsqueeze(2)  # [n, M, 1, D], lag n-1 first
+        y = torch.zeros((n, M, B, D), dtype=torch.float64, device=DEVICE)
+        out = torch.empty_like(y)
+        if kind == "synth":
+            w_up, b_up, w_down, b_down = (w.double() for w in _weights(case, seed))
+            eps = _noise(case, seed).double()
+        else:
+            x = _inputs(case, seed).double()
+        for t in range(n):
+            for m in range(M):
+                if kind == "synth":
+                    y[t, m] = out[t, m - 1] if m else eps[t] + (out[t - 1, M - 1] if t else 0.0)
+                else:
+                    prev = out[t, m - 1] if m else (out[t - 1, M - 1] if t else None)
+                    y[t, m] = x[t, m] if prev is None else x[t, m] + 0.5 * torch.tanh(prev)
+                z = (y[:t + 1, m] * hrev[n - 1 - t:, m]).sum(0)
+                if kind == "synth":
+                    hid = torch.nn.functional.gelu(z @ w_up[m].T + b_up[m])
+                    z = hid @ w_down[m].T + b_down[m]
+                out[t, m] = z
+        return out
+    y = _inputs(case, seed)
+    n = y.shape[0]
+    return _conv_all(y, lambda m, a, b: h[m, a:b, :n].T.unsqueeze(1))
