@@ -20,6 +20,7 @@ import torch
 import paper_2410_12982_amd.lcsm as lcsm
 
 DEVICE = "cuda:0"
+_stream = None
 # positions recorded per torch graph (graphs of more than about 16k kernel nodes are avoided)
 SEGMENT = {"dd": 2048, "synth": 64}
 
@@ -150,6 +151,15 @@ def _inputs(case, seed):
 
 # ----------------------------------------------------------- prepare, run
 
+def _program_stream():
+    """The stream a program does all of its work on (recording graphs needs one of its own), so that nothing has to
+    wait for another stream."""
+    global _stream
+    if _stream is None:
+        _stream = torch.cuda.Stream(DEVICE)
+    return torch.cuda.stream(_stream)
+
+
 def _record(stream, n, seg, step, reset):
     """Positions 0 .. n-1 as a chain of graphs, the first one starting with the reset."""
     graphs = []
@@ -166,32 +176,38 @@ def _record(stream, n, seg, step, reset):
 
 
 def prepare(case, seed):
+    with _program_stream():
+        return _prepare(case, seed)
+
+
+def _prepare(case, seed):
     kind, M, B, D, L = case["kind"], case["M"], case["B"], case["D"], case["L"]
     if kind == "dd":
         y, rho = _slabs(case, seed, L, 1), _rho(case, seed)
         z = torch.empty_like(y)
-        stream = torch.cuda.Stream(DEVICE)
-        ctx = lcsm.Dd(M, B, D, L, stream=stream, device=DEVICE)
-        graphs = _record(stream, L, SEGMENT[kind], lambda t: ctx.step(y[t], rho[t], z[t]), ctx.reset)
+        ctx = lcsm.Dd(M, B, D, L, device=DEVICE)
+        graphs = _record(ctx.stream, L, SEGMENT[kind], lambda t: ctx.step(y[t], rho[t], z[t]), ctx.reset)
         return dict(kind=kind, ctx=ctx, graphs=graphs, y=y, rho=rho, z=z)
     if kind == "synth":
         eps = _noise(case, seed)
         act = torch.empty((case["n"], M, B, D), device=DEVICE)
-        stream = torch.cuda.Stream(DEVICE)
-        ctx = lcsm.Synth(_filters(case, seed), *_weights(case, seed), B, stream=stream)
-        graphs = _record(stream, case["n"], SEGMENT[kind], lambda t: ctx.step(eps[t], act[t]), ctx.reset)
+        ctx = lcsm.Synth(_filters(case, seed), *_weights(case, seed), B)
+        graphs = _record(ctx.stream, case["n"], SEGMENT[kind], lambda t: ctx.step(eps[t], act[t]), ctx.reset)
         return dict(kind=kind, ctx=ctx, graphs=graphs, eps=eps, z=act)
     y = _inputs(case, seed)
     z = torch.empty_like(y)
+    ctx = lcsm.Lcsm(_filters(case, seed), B, options={"half_state": 1} if case.get("half") else None)
     if kind == "graph":
-        stream = torch.cuda.Stream(DEVICE)
-        ctx = lcsm.Lcsm(_filters(case, seed), B, options={"half_state": 1} if case["half"] else None, stream=stream)
         return dict(kind=kind, ctx=ctx, graph=ctx.capture(y, z, n=L, chain=case["chain"]), y=y, z=z)
-    ctx = lcsm.Lcsm(_filters(case, seed), B)
     return dict(kind=kind, ctx=ctx, y=y, z=z, P=case.get("P", 0))
 
 
 def run(state):
+    with _program_stream():
+        return _run(state)
+
+
+def _run(state):
     kind, ctx, z = state["kind"], state["ctx"], state["z"]
     if kind in ("dd", "synth"):
         for g in state["graphs"]:
@@ -199,7 +215,6 @@ def run(state):
         return z
     if kind == "graph":
         state["graph"].launch()
-        torch.cuda.current_stream(DEVICE).wait_stream(ctx.stream)
         return z
     y, P = state["y"], state["P"]
     ctx.reset()
