@@ -48,7 +48,7 @@ typedef struct lcsm_synth lcsm_synth;
  * 4 (16-byte weight rows).  opt is passed to the mixer (lcsm_options,
  * NULL for the defaults).  The library allocates its device memory (the
  * mixer's workspace, a copy of the weights, M*(4D*D + 3D) floats, and
- * (4 B D) floats of buffers).  Errors: LCSM_EINVAL (null pointers, D not a
+ * 3 B' D + B D floats of buffers, B' the batch rounded up to 4).  Errors: LCSM_EINVAL (null pointers, D not a
  * multiple of 4, or what lcsm_init rejects), LCSM_ENOMEM, LCSM_EDEVICE;
  * *out is NULL on failure. */
 int lcsm_synth_init(lcsm_synth** out, const float* filters, const float* w_up, const float* b_up,

@@ -6,29 +6,22 @@
 // Per position t the work is (all on the mixer context's stream):
 //   k_synth_red0            y^0_t = eps_t (+ a^M_{t-1}); layer 0's red cell
 //   for each layer m:
-//     k_gemv<UP>            hid = gelu(W_up[m] z^m_t + b_up[m])        [B][2D]
-//     k_gemv<DOWN>          a^{m+1}_t = W_down[m] hid + b_down[m] -> act[m];
+//     k_prod<UP>            hid = gelu(W_up[m] z^m_t + b_up[m])        [B][2D]
+//     k_prod<DOWN>          a^{m+1}_t = W_down[m] hid + b_down[m] -> act[m];
 //                           its epilogue is layer m+1's red cell (y^{m+1}_t =
 //                           a^{m+1}_t), or keeps a^M_t for the sampler
 //   the gray tiles of i = t+1 for all layers (the mixer's batched launch).
 //
-// The products are matrix-vector products over B <= 16 rows at a time: their
-// time is the weight read (4 bytes per weight, 2B flops).  Small ones are
-// bound by how many loads are in flight, not by bytes: a workgroup takes one
-// output unit and splits its weight row over K/256 waves, one 1 KB piece per
-// wave (its 64 lanes in 16-byte parts), multiplied with the same pieces of
-// the B input rows; each wave reduces with butterfly shuffles and wave 0 sums
-// the waves' partials from LDS in wave order (deterministic), after which
-// lane r stores row r.  With 8 and more rows against large weight matrices
-// that form is bound by re-reading the input rows for every unit, and the
-// products take the matrix cores instead (k_gemm16: 16 units per
-// workgroup, the 16 x 16 block of rows and units accumulated in four
-// registers per lane), which read the inputs once per 16 units.
+// The products are matrix-vector products over B <= 16 rows at a time (k_prod):
+// their time is the weight read (4 bytes per weight, 2B flops) plus what every
+// dependent launch costs, so a workgroup puts its whole share of the weights
+// in flight at once and nothing follows the sums but the stores.
 #include <math.h>
 #include <stdio.h>
 #include <string.h>
 
 #include <new>
+#include <type_traits>
 
 #include "lcsm_internal.h"
 #include "lcsm_synth.h"
@@ -36,7 +29,8 @@
 namespace lcsm {
 namespace {
 
-constexpr int kGemvMaxThreads = 1024;  // 16 waves: K up to 4096 in one piece per wave
+constexpr int kProdMaxThreads = 1024;
+constexpr int kProdCus = 256;    // compute units to fill
 constexpr int kMaxRows = 16;     // batch rows per product launch
 
 enum { kUp = 0, kDown = 1 };
@@ -46,9 +40,18 @@ enum { kUp = 0, kDown = 1 };
 struct RedNext {
   float* S;          // state slot row of position t, layer m+1: S + (m+1)*SL*BD + t*BD
   const float* h0;   // filter taps h[m+1, d, 0] (lag-0 row of layer m+1)
-  float* z;          // [B][D] the next layer's mixer output
+  float* z;          // the next layer's mixer output, quad layout
   float* last;       // [B][D] a^M_t (last layer only)
 };
+
+// Quad layout of a matrix of rows of K values (K a multiple of 4): four rows
+// at a time, four consecutive values of each in turn, [row / 4][k / 4][row % 4][4].
+// 16 consecutive lanes of k_prod then read one 256-byte run; with rows of K
+// floats they met four lines, and the products were bound by that (16 rows,
+// 2048 x 4096: 14.5 us, of which 4.5 us for the inputs' loads alone).
+__device__ __forceinline__ size_t quad_at(int row, int k, int K) {
+  return (size_t)(row >> 2) * 4 * K + (size_t)(k >> 2) * 16 + (row & 3) * 4 + (k & 3);
+}
 
 __device__ __forceinline__ float gelu(float v) {
   return 0.5f * v * (1.0f + erff(v * 0.70710678118654752f));
@@ -57,158 +60,195 @@ __device__ __forceinline__ float gelu(float v) {
 // out rows r < nrows of the product W [N][K] x^T with x [nrows][K] (row
 // stride K): MODE kUp -> out[r][n] = gelu(sum + bias[n]) (row stride N);
 // MODE kDown -> a = sum + bias[n], out[r][n] = a (row stride N = D), then the
-// red cell of the next layer or the sampler copy.  NR >= nrows, a power of
-// two <= kMaxRows; rows nrows..NR-1 are computed from row nrows-1 and not
-// stored.  K must be a multiple of 4 and the rows 16-byte aligned.
-// One output unit per workgroup: its WPU waves take consecutive 256-float
-// pieces of the unit's weight row (wave w: pieces w, w + WPU, ...), reduce
-// over the wave with butterfly shuffles, and wave 0 sums the WPU partials of
-// each row from LDS (in wave order: deterministic).
-template <int NR, int MODE>
-__global__ __launch_bounds__(kGemvMaxThreads) void k_gemv(const float* __restrict__ x,
+// red cell of the next layer or the sampler copy.  nrows <= 4 RG; rows past
+// nrows and units past N are computed from the last one and not stored.  K
+// must be a multiple of 4.  W, and x of kUp and kDown alike, are in the quad
+// layout (quad_at); kUp writes out in it, kDown row by row.
+//
+// A workgroup takes 4 UG output units; its waves split K into chunks of 64
+// (wave w: chunks w, w + nw, ...).  One v_mfma_f32_4x4x1_16b multiplies, in
+// each of its 16 blocks, one k of 4 rows with the same k of 4 units, so lane
+// 4 b + j holds four consecutive k of block b of unit j (and of row j) in one
+// 16-byte load and feeds four of them: a load of the wave is 256 contiguous
+// bytes of 4 rows, an input row is read once per 4 UG units, and a quad of
+// rows fills the matrix operand (a 16x16 block would be three quarters empty
+// at 4 rows).  The 16 blocks of a wave are summed with permlane swaps, each
+// halving the registers that still have to be summed, and two rotations in
+// the rows of 16 lanes; the waves' sums meet in LDS and are added in a fixed
+// order (deterministic).  The epilogue's operands (bias, next red cell) are
+// loaded first, under the weights.
+//
+// In a chain of launches over matrices out of the caches: 4 rows against 768 x
+// 1536 3.5 us (1.3 TB/s; a bare read of it, launch included, takes 2.4), 16
+// rows against 2048 x 4096 11.0 us (3.0 TB/s; bare read 6.7).  The model of 18
+// layers, 4 rows, 768 channels went from 168 to 123 us per position, that of 32
+// layers, 16 rows, 2048 channels from 1016 to 717 us.  What is left above the
+// reads is the inputs' traffic from L2 (16 rows of K per workgroup) and the
+// serial end: sums, barrier, epilogue, store.
+typedef float v4f __attribute__((ext_vector_type(4)));
+
+template <int CTRL>
+__device__ __forceinline__ float dpp_add(float v) {
+  const int o = __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xf, 0xf, false);
+  return v + __builtin_bit_cast(float, o);
+}
+
+// a + b after exchanging a's upper with b's lower 32 lanes: lanes 0..31 hold
+// a's two halves summed, lanes 32..63 b's.
+__device__ __forceinline__ float swap_add32(float a, float b) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(unsigned, a),
+                                                  __builtin_bit_cast(unsigned, b), false, false);
+  const unsigned lo = r[0], hi = r[1];
+  return __builtin_bit_cast(float, lo) + __builtin_bit_cast(float, hi);
+}
+// The same with the odd rows of 16 lanes of a and the even ones of b.
+__device__ __forceinline__ float swap_add16(float a, float b) {
+  const auto r = __builtin_amdgcn_permlane16_swap(__builtin_bit_cast(unsigned, a),
+                                                  __builtin_bit_cast(unsigned, b), false, false);
+  const unsigned lo = r[0], hi = r[1];
+  return __builtin_bit_cast(float, lo) + __builtin_bit_cast(float, hi);
+}
+
+template <int RG, int UG, int MODE>
+__global__ __launch_bounds__(kProdMaxThreads) void k_prod(const float* __restrict__ x,
                                                           const float* __restrict__ W,
                                                           const float* __restrict__ bias,
                                                           float* __restrict__ out, int N, int K,
                                                           int nrows, RedNext rn) {
-  __shared__ float part[kGemvMaxThreads / 64][NR];
-  const int lane = (int)threadIdx.x & 63, wv = (int)threadIdx.x >> 6;
-  const int wpu = (int)blockDim.x >> 6;
-  const int n = (int)blockIdx.x;
-  const float* wr = W + (size_t)n * K;
-  const float* xr[NR];
-#pragma unroll
-  for (int r = 0; r < NR; ++r) xr[r] = x + (size_t)(r < nrows ? r : nrows - 1) * K;
-  float acc[NR];
-#pragma unroll
-  for (int r = 0; r < NR; ++r) acc[r] = 0.f;
-  for (int k = wv * 256 + lane * 4; k < K; k += wpu * 256) {
-    const float4 w = *reinterpret_cast<const float4*>(wr + k);
-    float4 v[NR];
-#pragma unroll
-    for (int r = 0; r < NR; ++r) v[r] = *reinterpret_cast<const float4*>(xr[r] + k);
-#pragma unroll
-    for (int r = 0; r < NR; ++r) {
-      acc[r] = fmaf(w.x, v[r].x, acc[r]);
-      acc[r] = fmaf(w.y, v[r].y, acc[r]);
-      acc[r] = fmaf(w.z, v[r].z, acc[r]);
-      acc[r] = fmaf(w.w, v[r].w, acc[r]);
+  constexpr int NU = 4 * UG, NO = NU * 4 * RG;  // units, outputs of a workgroup
+  constexpr int R = 4 * RG * UG;                // partial sums per lane
+  constexpr int NA = RG * UG <= 2 ? 4 : 2;      // sums side by side: shorter chains
+  __shared__ float part[kProdMaxThreads / 64][NO];
+  const int tid = (int)threadIdx.x;
+  const int lane = tid & 63;
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int nw = (int)blockDim.x >> 6;
+  const int n0 = (int)blockIdx.x * NU;
+  const int k4 = (lane >> 2) * 4;  // the lane's k in a chunk; its unit and row of a quad: lane % 4
+
+  // output of this thread: for kUp in the order of the quads it writes
+  const int orow = MODE == kUp ? tid / (4 * NU) * 4 + tid / 4 % 4 : tid / NU;
+  const int ou = MODE == kUp ? tid / 16 % UG * 4 + tid % 4 : tid % NU;
+  const int on = n0 + ou;
+  const bool ohas = tid < NO && orow < nrows && on < N;
+  const size_t oe = (size_t)orow * N + on;
+  float obias = 0.f, oh0 = 0.f, oslot = 0.f;
+  if (ohas) {
+    obias = bias[on];
+    if constexpr (MODE == kDown) {
+      if (rn.S) {
+        oh0 = rn.h0[on];
+        oslot = rn.S[oe];
+      }
     }
   }
+
+  const float* wp[UG];
+  const float* xp[RG];
 #pragma unroll
-  for (int r = 0; r < NR; ++r) {
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) acc[r] += __shfl_xor(acc[r], off, 64);
+  for (int u = 0; u < UG; ++u) {
+    const int q = n0 / 4 + u;
+    wp[u] = W + (size_t)(4 * q < N ? q : N / 4 - 1) * 4 * K + 4 * lane;
   }
-  if (lane < NR) {
 #pragma unroll
-    for (int r = 0; r < NR; ++r)
-      if (r == lane) part[wv][r] = acc[r];
+  for (int g = 0; g < RG; ++g) xp[g] = x + (size_t)g * 4 * K + 4 * lane;
+  v4f acc[NA][UG][RG];
+#pragma unroll
+  for (int n = 0; n < NA; ++n)
+#pragma unroll
+    for (int u = 0; u < UG; ++u)
+#pragma unroll
+      for (int g = 0; g < RG; ++g) acc[n][u][g] = v4f{0.f, 0.f, 0.f, 0.f};
+
+  auto chunk = [&](int c, auto tail) {
+    constexpr bool TAIL = decltype(tail)::value;  // some k are past K: zeros on both sides
+    const bool in = !TAIL || 64 * c + k4 < K;
+    auto load = [&](const float* p) -> v4f {
+      const v4f v = *reinterpret_cast<const v4f*>(in ? p + 256 * c : p - 4 * lane);
+      return in ? v : v4f{0.f, 0.f, 0.f, 0.f};
+    };
+    v4f w[UG], xv[RG];
+#pragma unroll
+    for (int g = 0; g < RG; ++g) xv[g] = load(xp[g]);
+#pragma unroll
+    for (int u = 0; u < UG; ++u) w[u] = load(wp[u]);
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+#pragma unroll
+      for (int u = 0; u < UG; ++u)
+#pragma unroll
+        for (int g = 0; g < RG; ++g) {
+          v4f& a = acc[e % NA][u][g];
+          a = __builtin_amdgcn_mfma_f32_4x4x1f32(xv[g][e], w[u][e], a, 0, 0, 0);
+        }
+  };
+  int c = wv;
+  for (; 64 * (c + 1) <= K; c += nw) chunk(c, std::false_type{});
+  if (64 * c < K) chunk(c, std::true_type{});
+  // the epilogue's operands have arrived with the weights: not loaded later
+  asm volatile("" : "+v"(obias), "+v"(oh0), "+v"(oslot));
+
+  // sum i of the lane: unit 4 (i / (4 RG)) + j, row i % (4 RG)
+  float s[R];
+#pragma unroll
+  for (int i = 0; i < R; ++i) {
+    const int u = i / (4 * RG), g = i / 4 % RG, e = i % 4;
+    s[i] = acc[0][u][g][e];
+    s[i] += acc[1][u][g][e];
+    if constexpr (NA == 4) s[i] += acc[2][u][g][e] + acc[3][u][g][e];
+  }
+#pragma unroll
+  for (int i = 0; i < R / 2; ++i) s[i] = swap_add32(s[i], s[i + R / 2]);
+#pragma unroll
+  for (int i = 0; i < R / 4; ++i) s[i] = swap_add16(s[i], s[i + R / 4]);
+#pragma unroll
+  for (int i = 0; i < R / 4; ++i) s[i] = dpp_add<0x128>(dpp_add<0x124>(s[i]));
+  if ((lane & 12) == 0) {
+    const int i0 = ((lane >> 4) & 1) * (R / 4) + (lane >> 5) * (R / 2);
+#pragma unroll
+    for (int i = 0; i < R / 4; ++i) {
+      const int si = i0 + i;
+      part[wv][(si % (4 * RG)) * NU + 4 * (si / (4 * RG)) + (lane & 3)] = s[i];
+    }
   }
   __syncthreads();
-  if (wv != 0 || lane >= nrows) return;
-  const int r = lane;
-  float s = 0.f;
-  for (int q = 0; q < wpu; ++q) s += part[q][r];
-  s += bias[n];
-  const size_t e = (size_t)r * N + n;
+  if (!ohas) return;
+  float ps[4] = {0.f, 0.f, 0.f, 0.f};
+  const float* po = &part[0][orow * NU + ou];
+  int w = 0;
+  for (; w + 4 <= nw; w += 4)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) ps[i] += po[(w + i) * NO];
+  for (; w < nw; ++w) ps[0] += po[w * NO];
+  const float sum = ((ps[0] + ps[1]) + (ps[2] + ps[3])) + obias;
   if constexpr (MODE == kUp) {
-    out[e] = gelu(s);
+    out[quad_at(orow, on, N)] = gelu(sum);
   } else {
-    out[e] = s;
+    out[oe] = sum;
     if (rn.S) {
-      float* slot = rn.S + e;
-      rn.z[e] = fmaf(rn.h0[n], s, *slot);
-      *slot = s;
+      rn.z[quad_at(orow, on, N)] = fmaf(oh0, sum, oslot);
+      rn.S[oe] = sum;
     } else {
-      rn.last[e] = s;
+      rn.last[oe] = sum;
     }
   }
 }
 
-// The same product on the matrix cores, for several batch rows: a
-// workgroup takes 16 output units (or 8, with the block's other 8 columns
-// repeating them, where 16 would leave compute units idle) and splits K over
-// its waves; each wave
-// accumulates the 16 x 16 block (rows x units) of its K-slice with
-// v_mfma_f32_16x16x4f32, 16 k per step (lane l loads 4 consecutive k of
-// unit n0 + l%16 and of row l%16 at offset 4 (l/16); the four products of a
-// step take the four components, the same k on both operands).  The input
-// rows are then read once per 16 units instead of once per unit, and no
-// lane reductions are needed.  The waves' blocks are summed from LDS in
-// wave order (deterministic), then the same epilogue as k_gemv.  Rows past
-// nrows and units past N load clamped rows and are not stored; K is a
-// multiple of 4.
-typedef float v4f __attribute__((ext_vector_type(4)));
-
-template <int MODE>
-__global__ __launch_bounds__(kGemvMaxThreads) void k_gemm16(const float* __restrict__ x,
-                                                            const float* __restrict__ W,
-                                                            const float* __restrict__ bias,
-                                                            float* __restrict__ out, int N, int K,
-                                                            int nrows, int ut, RedNext rn) {
-  __shared__ float part[kGemvMaxThreads / 64][256];
-  const int lane = (int)threadIdx.x & 63, wv = (int)threadIdx.x >> 6;
-  const int nw = (int)blockDim.x >> 6;
-  const int n0 = (int)blockIdx.x * ut;  // ut = 16 units per workgroup, or 8 (columns 8..15 repeat them)
-  const int j = lane & 15, q = lane >> 4;
-  const int ju = j < ut ? j : j - ut;
-  const int un = n0 + ju < N ? n0 + ju : N - 1;  // unit whose weights this lane loads
-  const int xr = j < nrows ? j : nrows - 1;     // batch row whose inputs this lane loads
-  const float* wrow = W + (size_t)un * K + 4 * q;
-  const float* xrow = x + (size_t)xr * K + 4 * q;
-  // the wave's k-blocks of 16: a contiguous range
-  const int nkb = (K + 15) / 16;
-  const int per = (nkb + nw - 1) / nw;
-  const int kb0 = wv * per, kb1 = kb0 + per < nkb ? kb0 + per : nkb;
-  v4f acc = {0.f, 0.f, 0.f, 0.f};
-  // four k-blocks' loads in flight, then their 16 products
-  for (int kb = kb0; kb < kb1; kb += 4) {
-    float4 wf[4], xf[4];
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const int k = 16 * (kb + u);
-      wf[u] = xf[u] = make_float4(0.f, 0.f, 0.f, 0.f);
-      if (kb + u < kb1 && k + 4 * q < K) {
-        wf[u] = *reinterpret_cast<const float4*>(wrow + k);
-        xf[u] = *reinterpret_cast<const float4*>(xrow + k);
-      }
-    }
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      acc = __builtin_amdgcn_mfma_f32_16x16x4f32(xf[u].x, wf[u].x, acc, 0, 0, 0);
-      acc = __builtin_amdgcn_mfma_f32_16x16x4f32(xf[u].y, wf[u].y, acc, 0, 0, 0);
-      acc = __builtin_amdgcn_mfma_f32_16x16x4f32(xf[u].z, wf[u].z, acc, 0, 0, 0);
-      acc = __builtin_amdgcn_mfma_f32_16x16x4f32(xf[u].w, wf[u].w, acc, 0, 0, 0);
-    }
-  }
-  // lane (jj + 16 g) holds rows 4g .. 4g+3 of unit column jj
-#pragma unroll
-  for (int v = 0; v < 4; ++v) part[wv][(4 * q + v) * 16 + j] = acc[v];
-  __syncthreads();
-  for (int o = (int)threadIdx.x; o < 256; o += (int)blockDim.x) {
-    const int r = o >> 4, n = n0 + (o & 15);
-    if (r >= nrows || (o & 15) >= ut || n >= N) continue;
-    float sacc = 0.f;
-    for (int w = 0; w < nw; ++w) sacc += part[w][o];
-    const float sv = sacc + bias[n];
-    const size_t e = (size_t)r * N + n;
-    if constexpr (MODE == kUp) {
-      out[e] = gelu(sv);
-    } else {
-      out[e] = sv;
-      if (rn.S) {
-        float* slot = rn.S + e;
-        rn.z[e] = fmaf(rn.h0[n], sv, *slot);
-        *slot = sv;
-      } else {
-        rn.last[e] = sv;
-      }
-    }
+// dst = src [rows][K] in the quad layout (rows and K multiples of 4), one
+// thread per four values of a row.
+__global__ __launch_bounds__(256) void k_quads(const float* __restrict__ src,
+                                               float* __restrict__ dst, size_t rows, int K) {
+  const size_t n = rows * (size_t)(K / 4), step = (size_t)gridDim.x * 256;
+  for (size_t q = (size_t)blockIdx.x * 256 + threadIdx.x; q < n; q += step) {
+    // q counts the destination's quads: [row / 4][k / 4][row % 4]
+    const size_t g = q / K, r = q - g * K;  // K quads per four rows
+    const v4f v = *reinterpret_cast<const v4f*>(src + (4 * g + (r & 3)) * K + (r & ~(size_t)3));
+    *reinterpret_cast<v4f*>(dst + 4 * q) = v;
   }
 }
 
 // Sampler and layer 0's red cell at position t: y = eps (+ last for t > 0),
-// z = fmaf(h0[d], y, slot), slot = y.
+// z = fmaf(h0[d], y, slot) in the quad layout, slot = y.
 __global__ __launch_bounds__(256) void k_synth_red0(const float* __restrict__ eps,
                                                     const float* __restrict__ last,
                                                     float* __restrict__ slot_row,
@@ -217,51 +257,51 @@ __global__ __launch_bounds__(256) void k_synth_red0(const float* __restrict__ ep
   const int c = (int)blockIdx.x * 256 + (int)threadIdx.x;
   if (c >= BD) return;
   const float y = t > 0 ? last[c] + eps[c] : eps[c];
-  z[c] = fmaf(h0[c % D], y, slot_row[c]);
+  const int b = c / D, d = c - b * D;
+  z[quad_at(b, d, D)] = fmaf(h0[d], y, slot_row[c]);
   slot_row[c] = y;
 }
 
-// Which form a product takes.  The matrix-core form reads the input rows
-// once per 16 units, which pays where the per-unit form is bound by those
-// reads (8 and more rows against large weight matrices: 16 rows x 2048 x
-// 4096 ran 3.1x faster); on the latency-bound small products of 4 and 8 rows
-// x 768 it was 4-37 % slower (fewer waves in flight).
-inline bool gemm16_for(int N, int K, int nrows) {
-  return nrows >= 8 && (int64_t)N * K >= ((int64_t)1 << 22);
+hipError_t launch_quads(const float* src, float* dst, size_t rows, int K, hipStream_t st) {
+  size_t blocks = (rows * (size_t)(K / 4) + 255) / 256;
+  if (blocks > 16384) blocks = 16384;
+  hipLaunchKernelGGL(k_quads, dim3((unsigned)blocks), dim3(256), 0, st, src, dst, rows, K);
+  return hipGetLastError();
+}
+
+template <int RG, int MODE>
+hipError_t prod_rows(const float* x, const float* W, const float* bias, float* out, int N, int K,
+                     int nrows, const RedNext& rn, hipStream_t st) {
+  // 8 units per workgroup while that leaves three workgroups for every four
+  // CUs (the inputs are then read half as often), else 4: 16 rows against
+  // 2048 x 4096 take 11.4 against 13.5 us, 4 rows against 768 x 1536 3.6
+  // either way
+  const bool two = N >= 6 * kProdCus;
+  const int nch = (K + 63) / 64, outs = 16 * RG * (two ? 2 : 1);
+  // at most 16 waves, chunks shared evenly; 8 for the long rows, whose 16
+  // waves only compete (16 rows, 4096 x 2048: 10.3 against 11.4 us)
+  const int most = nch <= 24 ? kProdMaxThreads / 64 : 8;
+  const int rounds = (nch + most - 1) / most;
+  int threads = 64 * ((nch + rounds - 1) / rounds);
+  if (threads < outs) threads = (outs + 63) / 64 * 64;  // a thread per output
+  if (two)
+    hipLaunchKernelGGL((k_prod<RG, 2, MODE>), dim3((unsigned)((N + 7) / 8)), dim3(threads), 0, st, x,
+                       W, bias, out, N, K, nrows, rn);
+  else
+    hipLaunchKernelGGL((k_prod<RG, 1, MODE>), dim3((unsigned)((N + 3) / 4)), dim3(threads), 0, st, x,
+                       W, bias, out, N, K, nrows, rn);
+  return hipGetLastError();
 }
 
 template <int MODE>
-hipError_t gemv(const float* x, const float* W, const float* bias, float* out, int N, int K,
+hipError_t prod(const float* x, const float* W, const float* bias, float* out, int N, int K,
                 int nrows, const RedNext& rn, hipStream_t st) {
-  if (gemm16_for(N, K, nrows)) {
-    // 16 units per workgroup, about four k-blocks of 16 per wave, at most 16 waves
-    int nw = (K + 63) / 64;
-    if (nw > kGemvMaxThreads / 64) nw = kGemvMaxThreads / 64;
-    if (nw < 1) nw = 1;
-    // 8 units per workgroup where 16 would leave CUs idle (the column blocks
-    // 8..15 then repeat units 0..7 and are not stored)
-    const int ut = (N + 15) / 16 >= 256 ? 16 : 8;
-    hipLaunchKernelGGL((k_gemm16<MODE>), dim3((unsigned)((N + ut - 1) / ut)),
-                       dim3((unsigned)(64 * nw)), 0, st, x, W, bias, out, N, K, nrows, ut, rn);
-    return hipGetLastError();
+  switch ((nrows + 3) / 4) {
+    case 1: return prod_rows<1, MODE>(x, W, bias, out, N, K, nrows, rn, st);
+    case 2: return prod_rows<2, MODE>(x, W, bias, out, N, K, nrows, rn, st);
+    case 3: return prod_rows<3, MODE>(x, W, bias, out, N, K, nrows, rn, st);
+    default: return prod_rows<4, MODE>(x, W, bias, out, N, K, nrows, rn, st);
   }
-  int wpu = (K + 255) / 256;  // waves per unit: one 256-float piece each
-  if (wpu > kGemvMaxThreads / 64) wpu = kGemvMaxThreads / 64;
-  const dim3 grid((unsigned)N), block((unsigned)(64 * wpu));
-#define LCSM_GEMV(NR) \
-  hipLaunchKernelGGL((k_gemv<NR, MODE>), grid, block, 0, st, x, W, bias, out, N, K, nrows, rn)
-  if (nrows <= 1)
-    LCSM_GEMV(1);
-  else if (nrows <= 2)
-    LCSM_GEMV(2);
-  else if (nrows <= 4)
-    LCSM_GEMV(4);
-  else if (nrows <= 8)
-    LCSM_GEMV(8);
-  else
-    LCSM_GEMV(16);
-#undef LCSM_GEMV
-  return hipGetLastError();
 }
 
 }  // namespace
@@ -317,8 +357,9 @@ int lcsm_synth_init(lcsm_synth** out, const float* filters, const float* w_up, c
   const size_t D2 = 2 * (size_t)D, BD = (size_t)B * D;
   const size_t n_wup = (size_t)M * D2 * D, n_bup = (size_t)M * D2, n_wdn = (size_t)M * D * D2,
                n_bdn = (size_t)M * D;
+  const size_t B4 = ((size_t)B + 3) / 4 * 4;  // rows of the quad layout
   size_t off[7], total = 0;
-  const size_t sizes[7] = {n_wup, n_bup, n_wdn, n_bdn, BD, (size_t)B * D2, BD};
+  const size_t sizes[7] = {n_wup, n_bup, n_wdn, n_bdn, B4 * D, B4 * D2, BD};
   for (int k = 0; k < 7; ++k) {
     off[k] = total;
     total = align256(total + sizeof(float) * sizes[k]);
@@ -347,9 +388,12 @@ int lcsm_synth_init(lcsm_synth** out, const float* filters, const float* w_up, c
   }
   const float* src[4] = {w_up, b_up, w_down, b_down};
   hipError_t e = hipSuccess;
-  for (int k = 0; k < 4 && e == hipSuccess; ++k)
+  for (int k = 1; k < 4 && e == hipSuccess; k += 2)  // the biases
     e = hipMemcpyAsync(f[k], src[k], sizeof(float) * sizes[k], hipMemcpyDeviceToDevice, s->stream);
-  if (e == hipSuccess) e = lcsm::launch_zero(s->last, BD, s->stream);
+  if (e == hipSuccess) e = lcsm::launch_quads(w_up, s->w_up, (size_t)M * D2, D, s->stream);
+  if (e == hipSuccess) e = lcsm::launch_quads(w_down, s->w_down, (size_t)M * D, (int)D2, s->stream);
+  // z, hid and last (the rows past B of the last quad stay zero)
+  if (e == hipSuccess) e = lcsm::launch_zero(s->z, (total - off[4]) / sizeof(float), s->stream);
   if (e != hipSuccess) {
     (void)hipGetLastError();
     lcsm_destroy(s->mixer);
@@ -381,7 +425,7 @@ int lcsm_synth_step(lcsm_synth* s, const float* eps_t, float* act_t) {
     for (int r0 = 0; r0 < B && e == hipSuccess; r0 += lcsm::kMaxRows) {
       const int nr = B - r0 < lcsm::kMaxRows ? B - r0 : lcsm::kMaxRows;
       lcsm::RedNext none{nullptr, nullptr, nullptr, nullptr};
-      e = lcsm::gemv<lcsm::kUp>(s->z + (size_t)r0 * D, s->w_up + (size_t)m * D2 * D,
+      e = lcsm::prod<lcsm::kUp>(s->z + (size_t)r0 * D, s->w_up + (size_t)m * D2 * D,
                                 s->b_up + (size_t)m * D2, s->hid + (size_t)r0 * D2, D2, D, nr,
                                 none, st);
       lcsm::RedNext rn{nullptr, nullptr, nullptr, nullptr};
@@ -393,7 +437,7 @@ int lcsm_synth_step(lcsm_synth* s, const float* eps_t, float* act_t) {
         rn.last = s->last + (size_t)r0 * D;
       }
       if (e == hipSuccess)
-        e = lcsm::gemv<lcsm::kDown>(s->hid + (size_t)r0 * D2, s->w_down + (size_t)m * D * D2,
+        e = lcsm::prod<lcsm::kDown>(s->hid + (size_t)r0 * D2, s->w_down + (size_t)m * D * D2,
                                     s->b_down + (size_t)m * D,
                                     act_t + (size_t)m * BD + (size_t)r0 * D, D, D2, nr, rn, st);
     }

@@ -74,6 +74,24 @@ def test_synth_matches_oracle(shape):
     assert err <= TOL
 
 
+@pytest.mark.parametrize("B,D", [(1, 772), (4, 768), (5, 4), (6, 1540), (11, 64), (16, 260), (13, 768)])
+def test_synth_product_edges(B, D):
+    """The block products at the edges of their tiles: 1 to 16 rows (a quad of
+    rows whole and ragged), 4 and 8 units per workgroup (from 1536 units), rows
+    that end inside a chunk of 64, one wave and several rounds of waves."""
+    M, L = 2, 12
+    say(f"[synth products] B={B} D={D}")
+    w = datagen.Workload("synth_edges", M, B, D, L, decay=4.0, seed=90 + B)
+    model = _make(w)
+    act = _gpu_run(model, datagen.noise_torch(w, dev()), L)
+    ref = _oracle(datagen.filters_np(w), datagen.mlp_weights_np(w), datagen.noise_np(w), M, B, D, L)
+    # sums of at most 2D fp32 products in chains of at most 2D/64 + 8, twice per layer
+    bound = 4 * M * (2 * D / 64 + 8) * 2.0 ** -24
+    err = rel_err(act.reshape(L, M, -1), ref)
+    say(f"  rel err {err:.3e}, bound {bound:.3e}")
+    assert err <= bound
+
+
 def test_synth_identity_blocks():
     """W_up = [I; -I], W_down = [I, -I], no biases: each block is the identity
     (gelu(x) - gelu(-x) = x) and the model is linear in the noise."""
