@@ -143,18 +143,29 @@ __global__ __launch_bounds__(kThreads) void k_step_fused(const float* __restrict
   }
 }
 
-// The chain's input rule y = x + 0.5 tanh(z), evaluated as
-// (x + 1/2) - 1/(1 + e^{2z}) (the same function: 0.5 tanh(z) = 1/2 -
-// 1/(1 + e^{2z})) from the hardware base-2 exponential and reciprocal (each
-// within about one ulp): no branch, and x + 1/2 is off the serial chain.
-// Absolute error below 3.3e-7 for |x| <= 3 (an fp32 model of these steps
-// with both hardware results off by one ulp either way, against fp64, on
-// 1.2M points with z over [-20, 20] and 1e-8 .. 32 of either sign); z = +inf
-// gives x + 1/2, z = -inf x - 1/2, NaN stays NaN.
-__device__ __forceinline__ float chain_y(float x, float z) {
-  const float e = __builtin_amdgcn_exp2f(2.8853900817779268f * z);  // e^{2z}
-  return (x + 0.5f) - __builtin_amdgcn_rcpf(1.f + e);
+// The chain's input rule y = x + 0.5 tanh(z), evaluated as (x + 1/2) - r,
+// r = 1/(1 + e^{2z}) (the same function: 0.5 tanh(z) = 1/2 - r), from the
+// hardware base-2 exponential and reciprocal (each within about one ulp).
+// What runs from layer to layer and position to position is not z but
+// s = 2 log2(e) z, and z = h_0 y + acc is affine in r, so with
+//   A = 2 log2(e) (h_0 (x + 1/2) + acc),  B = 2 log2(e) h_0
+// known beforehand the dependent chain of a layer is exp2, an addition, rcp
+// and one multiply-add: s = A - B r.  y and z follow from r off the chain.
+// Absolute error of y below 3.3e-7 for |x| <= 3 as a function of z; s differs
+// from 2 log2(e) z by the rounding of A (a few ulp of its terms).  z = +inf
+// gives x + 1/2, z = -inf x - 1/2, NaN stays NaN (a tap h_0 beyond 1.1e38, whose
+// B is infinite, gives NaN where z would be infinite).  At t = 0 layer 0's input
+// is x itself: x in place of x + 1/2 and r = 0.
+constexpr float kChainScale = 2.8853900817779268f;  // 2 log2(e)
+
+__device__ __forceinline__ float chain_r(float s) {
+  return __builtin_amdgcn_rcpf(1.f + __builtin_amdgcn_exp2f(s));
 }
+__device__ __forceinline__ float chain_xh(float x, bool first) { return first ? x : x + 0.5f; }
+__device__ __forceinline__ float chain_a(float h0, float xh, float acc) {
+  return kChainScale * fmaf(h0, xh, acc);
+}
+__device__ __forceinline__ float chain_b(float h0) { return kChainScale * h0; }
 
 template <int U>
 struct ChainChunk {
@@ -177,7 +188,7 @@ __global__ __launch_bounds__(kThreads) void k_chain_fused(const float* __restric
   const int c = (int)blockIdx.y * D + d;
   const size_t rs = (size_t)BD;
   const bool tile = (U > 0) && (dst_len > 0);
-  float zl = 0.f;  // z^{M-1}_{t-1} (loaded with the first chunk), then z^{m-1}_t
+  float sl = 0.f;  // s of z^{M-1}_{t-1} (loaded with the first chunk), then of z^{m-1}_t
   for (int m0 = 0; m0 < M; m0 += K) {
     float xv[K], acc[K], h0[K];
     float yb[K][NY], hh[K][NH], zo[K][NZ];
@@ -206,18 +217,20 @@ __global__ __launch_bounds__(kThreads) void k_chain_fused(const float* __restric
         }
       }
     }
-    if (m0 == 0) zl = prev[c];  // unused at t = 0
+    if (m0 == 0) sl = prev[c];  // unused at t = 0
     // the chain through the chunk, then its stores
 #pragma unroll
     for (int kk = 0; kk < K; ++kk) {
       const int m = m0 + kk;
       if (m < M) {
         float* col = S + (size_t)m * SL * BD + c;
-        const float yv = (m == 0 && t == 0) ? xv[kk] : chain_y(xv[kk], zl);
-        const float zv = fmaf(h0[kk], yv, acc[kk]);
-        z[(size_t)m * BD + c] = zv;
+        const bool first = m == 0 && t == 0;
+        const float xh = chain_xh(xv[kk], first);
+        const float r = first ? 0.f : chain_r(sl);
+        const float yv = xh - r;
+        z[(size_t)m * BD + c] = fmaf(h0[kk], yv, acc[kk]);
         col[(size_t)t * rs] = yv;
-        zl = zv;
+        sl = fmaf(-chain_b(h0[kk]), r, chain_a(h0[kk], xh, acc[kk]));
         if constexpr (U > 0) {
           if (tile) {
             yb[kk][U - 1] = yv;
@@ -235,7 +248,7 @@ __global__ __launch_bounds__(kThreads) void k_chain_fused(const float* __restric
       }
     }
   }
-  prev[c] = zl;
+  prev[c] = sl;
 }
 
 // The chained steps (lcsm_step_chain) of the positions [t0, t1) of one
@@ -248,25 +261,30 @@ __global__ __launch_bounds__(kThreads) void k_chain_fused(const float* __restric
 // registers from the first position to the last, and no position of the
 // stretch moves a tile's operands through memory.
 //
-// A workgroup owns kChainBlockCols (b, d) columns of every layer.  Wave 0
-// walks the chain through the layers (y^m_t, z^m_t as k_chain_fused) on its
-// first kChainBlockCols lanes; wave w >= 1 holds layers 2(w-1) and
-// 2(w-1)+1, one per half.  Each lane of a layer wave keeps v[k] = state row
-// b + k of its column (y for positions already taken, the accumulator
-// otherwise) and the lags 1 .. kChainBlockW - 1 of its channel.  Per
-// position t = b + r: the layer waves hand acc_t and x_t over in LDS
-// (fetching x_{t+1}); wave 0 computes the chain and leaves z_t and y_t in
-// LDS, while the layer waves add the other output rows of the previous
-// position's tile; then each layer wave stores its layers' z_t and y_t
-// (W0S, for at most kChainBlockWave0StoreM layers: wave 0 stores them as
-// it goes instead) and computes the first output row of the tile of i = t+1 (the next
-// accumulator).  The tile arithmetic is that of k_step_fused<U, false> (per
-// output, the fmaf chain over the U inputs in increasing order, then added
-// to the accumulator), so the results equal the per-position steps bit for
-// bit.  The two barriers per position order LDS only: no wave reads global
-// memory another wave of the launch writes.  At the end the accumulator rows
-// at and after t1 (a stretch cut before its block ends) go back to the state.
-
+// Every lane that holds a column's block keeps v[k] = state row b + k (y for
+// positions already taken, the accumulator otherwise) and the lags 1 ..
+// kChainBlockW - 1 of its channel in registers.  The tile arithmetic is that
+// of k_step_fused<U, false> (per output, the fmaf chain over the U inputs in
+// increasing order, then added to the accumulator), so the results equal the
+// per-position steps bit for bit.  At the end the accumulator rows at and
+// after t1 (a stretch cut before its block ends) go back to the state.
+//
+// k_chain_lane, up to kChainLaneMaxM layers: a lane owns one column of every
+// layer and walks chain, red cells and tiles alone; nothing is exchanged.
+//
+// k_chain_block, above: a workgroup owns NC columns.  Wave 0 walks the chain,
+// the other waves hold 64 / NC layers each.  What bounds it is the chain, M
+// dependent layers per position and nothing beside it, so the layers are cut
+// into two halves and a position into two phases: while wave 0 walks one
+// half, the waves of the other half take what it left them (r), store y and z,
+// add the tile's first row (the next accumulator) and prepare A of the next
+// position, which wave 0 finds ready when it comes back.  A phase ends with a
+// barrier that orders LDS only (no wave reads global memory another wave of
+// the launch writes).  A tile's other rows and the part of the next first row
+// that does not need the newest input follow in the phase after, and x is
+// loaded kChainXAhead positions ahead.  18 layers x 3072 columns: 49.5 us per
+// 32 positions when each position's layer work ran between the chain's end
+// and its next start, 27.8 with the phases.
 // f(std::integral_constant<int, 0>{}), ..., f(std::integral_constant<int, N-1>{}).
 template <class F, int... R>
 __device__ __forceinline__ void static_for_impl(F& f, std::integer_sequence<int, R...>) {
@@ -284,17 +302,18 @@ __device__ __forceinline__ void chain_block_sync() {
 }
 
 // The tile of i = b + R + 1 (U = lowbit(R + 1)) on the register rows v, in
-// two parts: its first output row (R + 1, the accumulator the next
-// position's chain needs) and the rest (rows R + 2 .. R + U).  rem = L - i
-// clips the rows past the end.
+// three parts: of its first output row (R + 1, the accumulator the next
+// position's chain needs) the sum without the newest input, then that input's
+// term, and the rest (rows R + 2 .. R + U).  rem = L - i clips the rows past
+// the end.
 template <int R>
-__device__ __forceinline__ void chain_block_first_row(float (&v)[kChainBlockW],
-                                                      const float (&hh)[kChainBlockW]) {
+__device__ __forceinline__ float chain_block_first_part(const float (&v)[kChainBlockW],
+                                                        const float (&hh)[kChainBlockW]) {
   constexpr int U = (R + 1) & -(R + 1);
   float o = 0.f;
 #pragma unroll
-  for (int k = 0; k < U; ++k) o = fmaf(v[R + 1 - U + k], hh[U - k], o);
-  v[R + 1] = v[R + 1] + o;
+  for (int k = 0; k < U - 1; ++k) o = fmaf(v[R + 1 - U + k], hh[U - k], o);
+  return o;
 }
 
 template <int R>
@@ -312,131 +331,229 @@ __device__ __forceinline__ void chain_block_rest_rows(float (&v)[kChainBlockW],
   }
 }
 
-template <bool W0S>
-__global__ __launch_bounds__(64 * (1 + (kChainBlockMaxM + 1) / 2)) void k_chain_block(
+// Block rows and lags of one column of layer m (column c of the layer, rows
+// and lags past the end clamped, the lags zero).
+__device__ __forceinline__ void chain_block_load(const float* Sc, const float* hc, size_t rs,
+                                                 int D, int L, int b, float (&v)[kChainBlockW],
+                                                 float (&hh)[kChainBlockW], float& h0) {
+  constexpr int W = kChainBlockW;
+#pragma unroll
+  for (int k = 0; k < W; ++k) v[k] = Sc[(size_t)(b + k < L ? b + k : L - 1) * rs];
+  h0 = hc[0];
+  hh[0] = 0.f;
+#pragma unroll
+  for (int l = 1; l < W; ++l) {
+    const float hv = hc[(size_t)(l < L ? l : L - 1) * D];
+    hh[l] = l < L ? hv : 0.f;
+  }
+}
+
+template <int ML>
+__global__ __launch_bounds__(64) void k_chain_lane(
+    const float* __restrict__ x, size_t xst, int xring, int xs0, float* __restrict__ z,
+    size_t zst, int zring, int zs0, float* __restrict__ S, const float* __restrict__ Hf,
+    float* __restrict__ prev, int L, int SL, int BD, int D, int t0, int t1, int tile_last) {
+  constexpr int W = kChainBlockW;
+  const int c = (int)blockIdx.x * 64 + (int)threadIdx.x;
+  if (c >= BD) return;
+  const int d = c % D;
+  const size_t rs = (size_t)BD;
+  const int b = t0 & ~(W - 1);
+  const int r0 = t0 - b, r1 = t1 - b;
+  float v[ML][W], hh[ML][W], h0[ML], xv[ML][W];
+  // the block's inputs too, all at once: a position takes less than a load
+  {
+    int xs = xs0 % xring;
+#pragma unroll
+    for (int r = 0; r < W; ++r) {
+      const bool in = r >= r0 && r < r1;
+#pragma unroll
+      for (int m = 0; m < ML; ++m) xv[m][r] = x[(size_t)xs * xst + (size_t)m * BD + c];
+      if (in && r + 1 < r1) xs = xs + 1 == xring ? 0 : xs + 1;
+    }
+  }
+#pragma unroll
+  for (int m = 0; m < ML; ++m)
+    chain_block_load(S + (size_t)m * SL * BD + c, Hf + (size_t)m * L * D + d, rs, D, L, b, v[m],
+                     hh[m], h0[m]);
+  float sl = prev[c];  // unused at t = 0
+  int zs = zs0 % zring;
+  auto position = [&](auto rc) {
+    constexpr int r = decltype(rc)::value;
+    if (r < r0 || r >= r1) return;
+    const int t = b + r;
+    const bool tile = r + 1 < W && t + 1 < L && (r + 1 < r1 || tile_last);
+#pragma unroll
+    for (int m = 0; m < ML; ++m) {
+      const bool first = m == 0 && t == 0;
+      const float xh = chain_xh(xv[m][r], first);
+      const float rr = first ? 0.f : chain_r(sl);
+      const float yv = xh - rr;
+      sl = fmaf(-chain_b(h0[m]), rr, chain_a(h0[m], xh, v[m][r]));
+      z[(size_t)zs * zst + (size_t)m * BD + c] = fmaf(h0[m], yv, v[m][r]);
+      S[((size_t)m * SL + t) * rs + c] = yv;
+      v[m][r] = yv;
+      if constexpr (r + 1 < W) {
+        if (tile) {
+          const float o = fmaf(yv, hh[m][1], chain_block_first_part<r>(v[m], hh[m]));
+          v[m][r + 1] = v[m][r + 1] + o;
+          chain_block_rest_rows<r>(v[m], hh[m], L - (t + 1));
+        }
+      }
+    }
+    zs = zs + 1 == zring ? 0 : zs + 1;
+  };
+  static_for<W>(position);
+  prev[c] = sl;
+#pragma unroll
+  for (int m = 0; m < ML; ++m)
+#pragma unroll
+    for (int k = 0; k < W; ++k)
+      if (k >= r1 && b + k < L) S[((size_t)m * SL + b + k) * rs + c] = v[m][k];
+}
+
+// Layers of the first half: whole waves of LPW layers, at least one in each half.
+template <int LPW>
+constexpr int chain_half(int M) {
+  return (M + LPW) / (2 * LPW) * LPW;
+}
+
+// Wave 0 of k_chain_block for M layers known at compile time: the dependent
+// chain without a branch in it (with the layer count in a register, a jump per
+// layer and half made it 1.3 times slower).  Phase h: half h's layers in order,
+// then the barrier.
+template <int M, int NC, int HM>
+__device__ __forceinline__ float chain_walk(const float (*abuf)[NC], const float (*bbuf)[NC],
+                                            float (*rbuf)[NC], int col, float sl, bool first,
+                                            int n) {
+  constexpr int H = chain_half<64 / NC>(M);
+  float bv[M];
+#pragma unroll
+  for (int m = 0; m < M; ++m) bv[m] = bbuf[m < H ? m : HM + m - H][col];
+  for (; n > 0; --n) {
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int m0 = h ? H : 0, m1 = h ? M : H;
+      float av[HM];
+#pragma unroll
+      for (int m = m0; m < m1; ++m) av[m - m0] = abuf[h * HM + m - m0][col];
+#pragma unroll
+      for (int m = m0; m < m1; ++m) {
+        float rr = chain_r(sl);
+        if (m == 0) rr = first ? 0.f : rr;
+        rbuf[h * HM + m - m0][col] = rr;  // lanes of one column write the same value
+        sl = fmaf(-bv[m], rr, av[m - m0]);
+      }
+      chain_block_sync();
+    }
+    first = false;
+  }
+  return sl;
+}
+
+// HM: layers of the larger half at most; ML0 .. ML1 the layer counts.
+template <int NC, int HM, int ML0, int ML1>
+__global__ __launch_bounds__(64 * (1 + (ML1 + 64 / NC - 1) / (64 / NC))) void k_chain_block(
     const float* __restrict__ x, size_t xst, int xring, int xs0, float* __restrict__ z,
     size_t zst, int zring, int zs0, float* __restrict__ S, const float* __restrict__ Hf,
     float* __restrict__ prev, int M, int L, int SL, int BD, int D, int t0, int t1,
     int tile_last) {
-  constexpr int NC = kChainBlockCols, W = kChainBlockW;
-  __shared__ float2 axbuf[kChainBlockMaxM][NC];  // (acc_t, x_t)
-  __shared__ float2 yzbuf[kChainBlockMaxM][NC];  // (y_t, z_t)
-  __shared__ float h0buf[kChainBlockMaxM][NC];
+  constexpr int W = kChainBlockW, LPW = 64 / NC, XA = kChainXAhead;
+  __shared__ float abuf[2 * HM][NC];  // A of the next position, by half and layer in it
+  __shared__ float bbuf[2 * HM][NC];  // B
+  __shared__ float rbuf[2 * HM][NC];  // r of the position taken last
   const int lane = (int)threadIdx.x & 63;
   const int wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
   const int col = lane & (NC - 1);
   const int c = (int)blockIdx.x * NC + col;
   const bool live = c < BD;
   const int cc = live ? c : BD - 1;
-  const int d = cc % D;
-  const size_t rs = (size_t)BD;
   const int b = t0 & ~(W - 1);
   const int r0 = t0 - b, r1 = t1 - b;
-  const int m = 2 * (wv - 1) + (lane >> 5);
-  const bool has = wv > 0 && m < M;
-  const int mc = has ? m : 0;
-  float* Sc = S + (size_t)mc * SL * BD + cc;
-  const float* hc = Hf + (size_t)mc * L * D + d;
-  const size_t xoff = (size_t)mc * BD + cc;
-  float v[W], hh[W];
-  float xn = 0.f;
-  if (has) {
-#pragma unroll
-    for (int k = 0; k < W; ++k) v[k] = Sc[(size_t)(b + k < L ? b + k : L - 1) * rs];
-    hh[0] = 0.f;
-#pragma unroll
-    for (int l = 1; l < W; ++l) {
-      const float hv = hc[(size_t)(l < L ? l : L - 1) * D];
-      hh[l] = l < L ? hv : 0.f;
-    }
-    h0buf[m][col] = hc[0];
-    xn = x[(size_t)(xs0 % xring) * xst + xoff];
-  } else {
-#pragma unroll
-    for (int k = 0; k < W; ++k) v[k] = hh[k] = 0.f;
+  const int H = chain_half<LPW>(M);
+  if (wv == 0) {
+    __builtin_amdgcn_s_setprio(3);
+    float sl = prev[cc];  // s of z^{M-1}_{t-1}; unused at t = 0
+    chain_block_sync();
+    auto walk = [&](auto mc) {
+      constexpr int MM = ML0 + decltype(mc)::value;
+      if (M == MM) sl = chain_walk<MM, NC, HM>(abuf, bbuf, rbuf, col, sl, t0 == 0, r1 - r0);
+    };
+    static_for<ML1 - ML0 + 1>(walk);
+    if (lane < NC && live) prev[c] = sl;
+    return;
   }
-  float zl = 0.f;  // chain wave: z^{M-1}_{t-1}, then z^{m-1}_t
-  if (wv == 0) zl = prev[cc];  // unused at t = 0
-  // whether the tile of position p (i = b + p + 1) runs in this launch
-  auto tile_of = [&](int p) {
-    return p >= r0 && p < r1 && p + 1 < W && b + p + 1 < L && (p + 1 < r1 || tile_last);
+  const int m = LPW * (wv - 1) + lane / NC;
+  const int half = LPW * (wv - 1) >= H ? 1 : 0;  // a wave's layers lie in one half
+  const bool has = m < M;
+  const int mc = has ? m : M - 1;
+  const int slot = half * HM + (mc - (half ? H : 0));
+  const int d = cc % D;
+  const size_t rs = (size_t)BD;
+  float* Sc = S + (size_t)mc * SL * BD + cc;
+  const float* xc = x + (size_t)mc * BD + cc;
+  float* zc = z + (size_t)mc * BD + cc;
+  const bool store = has && live;
+  float v[W], hh[W], h0, xq[XA];
+  // x of the next XA positions (past the stretch: its last one, unused)
+  int xs = xs0 % xring, xt = t0, zs = zs0 % zring;
+  auto next_x = [&]() {
+    const float xv = xc[(size_t)xs * xst];
+    if (++xt < t1) xs = xs + 1 == xring ? 0 : xs + 1;
+    return xv;
   };
-  // ring slabs of the current position's z and of the next position's x
-  int zsl = zs0 % zring, xsl = (xs0 + 1) % xring;
+#pragma unroll
+  for (int k = 0; k < XA; ++k) xq[k] = next_x();
+  chain_block_load(Sc, Hf + (size_t)mc * L * D + d, rs, D, L, b, v, hh, h0);
+  float xh = 0.f, part = 0.f;
+  // A of position r (its accumulator v[r] complete)
+  auto prepare = [&](int t, float acc, float xv) {
+    xh = chain_xh(xv, mc == 0 && t == 0);
+    if (has) abuf[slot][col] = chain_a(h0, xh, acc);
+  };
+  auto tile_of = [&](int r) { return r + 1 < W && b + r + 1 < L && (r + 1 < r1 || tile_last); };
+  auto begin = [&](auto rc) {
+    constexpr int r = decltype(rc)::value;
+    if (r != r0) return;
+    prepare(t0, v[r], xq[0]);
+    part = chain_block_first_part<r>(v, hh);
+  };
+  static_for<W>(begin);
+  if (has) bbuf[slot][col] = chain_b(h0);
+  chain_block_sync();
+  chain_block_sync();
+  if (half) chain_block_sync();
   auto position = [&](auto rc) {
     constexpr int r = decltype(rc)::value;
     if (r < r0 || r >= r1) return;
     const int t = b + r;
-    if (has) {
-      axbuf[m][col] = make_float2(v[r], xn);
-      if (r + 1 < r1) xn = x[(size_t)xsl * xst + xoff];
-      xsl = xsl + 1 == xring ? 0 : xsl + 1;
+    const float yv = xh - rbuf[slot][col];
+    const float zv = fmaf(h0, yv, v[r]);
+    v[r] = yv;
+    if constexpr (r + 1 < W) {
+      if (tile_of(r)) v[r + 1] = v[r + 1] + fmaf(yv, hh[1], part);
+#pragma unroll
+      for (int k = 0; k + 1 < XA; ++k) xq[k] = xq[k + 1];
+      prepare(t + 1, v[r + 1], xq[0]);
     }
-    chain_block_sync();
-    if (wv == 0) {
-      if (lane < NC) {
-        float* zq = z + (size_t)zsl * zst + c;
-        float* Sq = S + (size_t)t * rs + c;
-        const size_t ls = (size_t)SL * BD;
-        // layer q's inputs read two layers ahead of the chain
-        const int q1 = M > 1 ? 1 : 0;
-        float2 ax = axbuf[0][col], ax1 = axbuf[q1][col];
-        float h0 = h0buf[0][col], h01 = h0buf[q1][col];
-        for (int q = 0; q < M; ++q) {
-          const int qn = q + 2 < M ? q + 2 : M - 1;
-          const float2 ax2 = axbuf[qn][col];
-          const float h02 = h0buf[qn][col];
-          const float xv = ax.y, av = ax.x;
-          const float yv = (q == 0 && t == 0) ? xv : chain_y(xv, zl);
-          const float zv = fmaf(h0, yv, av);
-          if constexpr (W0S) {
-            if (live) {
-              zq[(size_t)q * BD] = zv;
-              Sq[(size_t)q * ls] = yv;
-            }
-          }
-          yzbuf[q][col] = make_float2(yv, zv);
-          zl = zv;
-          ax = ax1;
-          h0 = h01;
-          ax1 = ax2;
-          h01 = h02;
-        }
-      }
-    } else if (has && r >= 1) {
-      // the rest of the previous position's tile, beside the chain
-      if constexpr (r >= 1) {
-        if (tile_of(r - 1)) chain_block_rest_rows<r - 1>(v, hh, L - t);
-      }
+    if (store) {
+      zc[(size_t)zs * zst] = zv;
+      Sc[(size_t)t * rs] = yv;
     }
-    chain_block_sync();
-    if (has) {
-      const float2 yz = yzbuf[m][col];
-      const float yv = yz.x;
-      if constexpr (!W0S) {
-        if (live) {
-          z[(size_t)zsl * zst + (size_t)m * BD + c] = yz.y;
-          Sc[(size_t)t * rs] = yv;
-        }
-      }
-      v[r] = yv;
-      if constexpr (r + 1 < W) {
-        if (tile_of(r)) chain_block_first_row<r>(v, hh);
-      }
+    zs = zs + 1 == zring ? 0 : zs + 1;
+    if (r + 1 < r1) {
+      xq[XA - 1] = next_x();
+      chain_block_sync();
     }
-    zsl = zsl + 1 == zring ? 0 : zsl + 1;
+    if constexpr (r + 1 < W) {
+      if (tile_of(r)) chain_block_rest_rows<r>(v, hh, L - (t + 1));
+      part = chain_block_first_part<r + 1>(v, hh);
+    }
+    if (r + 1 < r1) chain_block_sync();
   };
   static_for<W>(position);
-  // the rest of the last position's tile
-  auto last_rest = [&](auto rc) {
-    constexpr int r = decltype(rc)::value;
-    if constexpr (r + 1 < W) {
-      if (r == r1 - 1 && tile_of(r)) chain_block_rest_rows<r>(v, hh, L - (b + r + 1));
-    }
-  };
-  if (has) static_for<W>(last_rest);
-  if (wv == 0 && lane < NC && live && r1 > r0) prev[c] = zl;
-  if (has && live) {
+  if (!half) chain_block_sync();
+  if (store) {
 #pragma unroll
     for (int k = 0; k < W; ++k)
       if (k >= r1 && b + k < L) Sc[(size_t)(b + k) * rs] = v[k];
@@ -653,14 +770,36 @@ hipError_t launch_chain_block(const float* x, size_t xst, int xring, int xs0, fl
                               hipStream_t st) {
   if (s.M > kChainBlockMaxM || t1 <= t0 || (t0 & ~(kChainBlockW - 1)) != ((t1 - 1) & ~(kChainBlockW - 1)))
     return hipErrorInvalidValue;
-  const int nw = 1 + (s.M + 1) / 2;
-  const dim3 grid((unsigned)((s.BD + kChainBlockCols - 1) / kChainBlockCols)), block((unsigned)(64 * nw));
-  if (s.M <= kChainBlockWave0StoreM)
-    hipLaunchKernelGGL(k_chain_block<true>, grid, block, 0, st, x, xst, xring, xs0, z, zst, zring,
-                       zs0, S, Hf, prev, s.M, s.L, s.SL, s.BD, s.D, t0, t1, tile_last ? 1 : 0);
+  const int tl = tile_last ? 1 : 0;
+#define LCSM_CHAIN_LANE(ML)                                                                        \
+  hipLaunchKernelGGL((k_chain_lane<ML>), dim3((unsigned)((s.BD + 63) / 64)), dim3(64), 0, st, x,   \
+                     xst, xring, xs0, z, zst, zring, zs0, S, Hf, prev, s.L, s.SL, s.BD, s.D, t0, t1, \
+                     tl)
+  if (s.M == 1) {
+    LCSM_CHAIN_LANE(1);
+    return hipGetLastError();
+  }
+  if (s.M == 2) {
+    LCSM_CHAIN_LANE(2);
+    return hipGetLastError();
+  }
+#undef LCSM_CHAIN_LANE
+#define LCSM_CHAIN_BLOCK(NC, HM, ML0, ML1)                                                        \
+  hipLaunchKernelGGL((k_chain_block<NC, HM, ML0, ML1>), dim3((unsigned)((s.BD + NC - 1) / NC)),   \
+                     dim3((unsigned)(64 * (1 + (s.M * NC + 63) / 64))), 0, st, x, xst, xring, xs0, \
+                     z, zst, zring, zs0, S, Hf, prev, s.M, s.L, s.SL, s.BD, s.D, t0, t1, tl)
+  // 16 columns per workgroup (half the waves, so the chain wave meets less
+  // company on its SIMD) while a workgroup per CU holds them all
+  const bool narrow = s.M >= 8 && (s.BD + 15) / 16 <= kChainBlockMaxGroups;
+  if (s.M <= 8 && !narrow)
+    LCSM_CHAIN_BLOCK(32, 4, 3, 8);
+  else if (s.M <= 16)
+    if (narrow) LCSM_CHAIN_BLOCK(16, 8, 8, 16); else LCSM_CHAIN_BLOCK(32, 8, 9, 16);
+  else if (s.M <= 22)
+    if (narrow) LCSM_CHAIN_BLOCK(16, 12, 17, 22); else LCSM_CHAIN_BLOCK(32, 12, 17, 22);
   else
-    hipLaunchKernelGGL(k_chain_block<false>, grid, block, 0, st, x, xst, xring, xs0, z, zst, zring,
-                       zs0, S, Hf, prev, s.M, s.L, s.SL, s.BD, s.D, t0, t1, tile_last ? 1 : 0);
+    if (narrow) LCSM_CHAIN_BLOCK(16, 16, 23, 30); else LCSM_CHAIN_BLOCK(32, 16, 23, 30);
+#undef LCSM_CHAIN_BLOCK
   return hipGetLastError();
 }
 

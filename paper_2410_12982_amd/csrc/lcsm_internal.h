@@ -58,13 +58,13 @@ hipError_t launch_chain_fused(const float* x, float* z, float* S, const float* H
 // tiles are direct with U <= kChainBlockW / 2 (the last position's tile only
 // when tile_last).  Position t reads x slab (xs0 + t - t0) mod xring and
 // writes z slab (zs0 + t - t0) mod zring.  Full-state contexts with at most
-// kChainBlockMaxM layers; a workgroup takes kChainBlockCols columns of every
-// layer, and the launch is used while the columns fill at most
+// kChainBlockMaxM layers; a workgroup takes up to kChainBlockCols columns of
+// every layer, and the launch is used while the columns fill at most
 // kChainBlockMaxGroups workgroups (one per compute unit: beyond that, the
 // serial chain of each workgroup makes one launch per position faster).
 constexpr int kChainBlockW = 32;
 constexpr int kChainBlockMaxM = 30;
-constexpr int kChainBlockWave0StoreM = 4;  // up to this many layers the chain wave stores z and y
+constexpr int kChainXAhead = 4;  // positions by which the chained inputs are loaded ahead
 constexpr int kChainBlockCols = 32;
 constexpr int kChainBlockMaxGroups = 256;
 hipError_t launch_chain_block(const float* x, size_t xst, int xring, int xs0, float* z,

@@ -78,6 +78,30 @@ def test_run_chain_equals_single_steps(shape, opts):
     ctx.close()
 
 
+@pytest.mark.parametrize("M,BD", [(M, BD) for M in (1, 2, 3, 7, 8, 9, 16, 17, 22, 23, 30)
+                                  for BD in (50, 4100)])
+def test_run_chain_forms(M, BD):
+    """Every form of the block launch at the edges of its layer counts (a lane
+    per column up to 2 layers, then two halves of whole waves) and at 16 and 32
+    columns per workgroup (above 4096 columns), last workgroup ragged: bit for
+    bit the single steps, a run cut inside a block included."""
+    say(f"[run_chain forms] M={M} BD={BD}")
+    L, D = 100, BD // 2
+    w = datagen.Workload("chainforms", M, 2, D, L, decay=L / 4, seed=M + BD)
+    x = datagen.x_torch(w, dev())
+    ctx = _ctx(w, None)
+    z_ref, z = torch.empty_like(x), torch.full_like(x, float("nan"))
+    with torch.cuda.stream(ctx.stream):
+        for t in range(L):
+            ctx.step_chain(x[t], z_ref[t])
+        ctx.reset()
+        ctx.run_chain(x[:45], z[:45])
+        ctx.run_chain(x[45:], z[45:])
+    torch.cuda.synchronize()
+    assert torch.equal(z, z_ref)
+    ctx.close()
+
+
 @pytest.mark.parametrize("name", ["m1b1d16l1k", "layers4"])
 def test_run_chain_matches_the_oracle_closed_loop(name):
     """The 1024-position workload, and 4 layers over 300 positions with
