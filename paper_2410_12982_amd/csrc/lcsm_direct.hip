@@ -147,25 +147,21 @@ __global__ __launch_bounds__(kThreads) void k_step_fused(const float* __restrict
 // r = 1/(1 + e^{2z}) (the same function: 0.5 tanh(z) = 1/2 - r), from the
 // hardware base-2 exponential and reciprocal (each within about one ulp).
 // What runs from layer to layer and position to position is not z but
-// s = 2 log2(e) z, and z = h_0 y + acc is affine in r, so with
-//   A = 2 log2(e) (h_0 (x + 1/2) + acc),  B = 2 log2(e) h_0
-// known beforehand the dependent chain of a layer is exp2, an addition, rcp
-// and one multiply-add: s = A - B r.  y and z follow from r off the chain.
-// Absolute error of y below 3.3e-7 for |x| <= 3 as a function of z; s differs
-// from 2 log2(e) z by the rounding of A (a few ulp of its terms).  z = +inf
-// gives x + 1/2, z = -inf x - 1/2, NaN stays NaN (a tap h_0 beyond 1.1e38, whose
-// B is infinite, gives NaN where z would be infinite).  At t = 0 layer 0's input
-// is x itself: x in place of x + 1/2 and r = 0.
+// s = 2 log2(e) z = B y + A with B = 2 log2(e) h_0 and A = 2 log2(e) acc known
+// beforehand, so the dependent chain of a layer is exp2, an addition, rcp, a
+// subtraction and one multiply-add, and z follows from y off the chain.  (One
+// operation less, s affine in r itself, rounds where h_0 (x + 1/2) cancels: 3 to
+// 5 % more error over closed loops.)  Absolute error of y below 3.3e-7 for |x|
+// <= 3.  z = +inf gives x + 1/2, z = -inf x - 1/2, NaN stays NaN (taps and
+// accumulators beyond 1.1e38 overflow in s and act as infinite).  At t = 0
+// layer 0's input is x itself: x in place of x + 1/2 and r = 0.
 constexpr float kChainScale = 2.8853900817779268f;  // 2 log2(e)
 
 __device__ __forceinline__ float chain_r(float s) {
   return __builtin_amdgcn_rcpf(1.f + __builtin_amdgcn_exp2f(s));
 }
 __device__ __forceinline__ float chain_xh(float x, bool first) { return first ? x : x + 0.5f; }
-__device__ __forceinline__ float chain_a(float h0, float xh, float acc) {
-  return kChainScale * fmaf(h0, xh, acc);
-}
-__device__ __forceinline__ float chain_b(float h0) { return kChainScale * h0; }
+__device__ __forceinline__ float chain_scaled(float v) { return kChainScale * v; }
 
 template <int U>
 struct ChainChunk {
@@ -230,7 +226,7 @@ __global__ __launch_bounds__(kThreads) void k_chain_fused(const float* __restric
         const float yv = xh - r;
         z[(size_t)m * BD + c] = fmaf(h0[kk], yv, acc[kk]);
         col[(size_t)t * rs] = yv;
-        sl = fmaf(-chain_b(h0[kk]), r, chain_a(h0[kk], xh, acc[kk]));
+        sl = fmaf(chain_scaled(h0[kk]), yv, chain_scaled(acc[kk]));
         if constexpr (U > 0) {
           if (tile) {
             yb[kk][U - 1] = yv;
@@ -276,7 +272,7 @@ __global__ __launch_bounds__(kThreads) void k_chain_fused(const float* __restric
 // the other waves hold 64 / NC layers each.  What bounds it is the chain, M
 // dependent layers per position and nothing beside it, so the layers are cut
 // into two halves and a position into two phases: while wave 0 walks one
-// half, the waves of the other half take what it left them (r), store y and z,
+// half, the waves of the other half take the y it left them, store y and z,
 // add the tile's first row (the next accumulator) and prepare A of the next
 // position, which wave 0 finds ready when it comes back.  A phase ends with a
 // barrier that orders LDS only (no wave reads global memory another wave of
@@ -389,7 +385,7 @@ __global__ __launch_bounds__(64) void k_chain_lane(
       const float xh = chain_xh(xv[m][r], first);
       const float rr = first ? 0.f : chain_r(sl);
       const float yv = xh - rr;
-      sl = fmaf(-chain_b(h0[m]), rr, chain_a(h0[m], xh, v[m][r]));
+      sl = fmaf(chain_scaled(h0[m]), yv, chain_scaled(v[m][r]));
       z[(size_t)zs * zst + (size_t)m * BD + c] = fmaf(h0[m], yv, v[m][r]);
       S[((size_t)m * SL + t) * rs + c] = yv;
       v[m][r] = yv;
@@ -423,8 +419,8 @@ constexpr int chain_half(int M) {
 // layer and half made it 1.3 times slower).  Phase h: half h's layers in order,
 // then the barrier.
 template <int M, int NC, int HM>
-__device__ __forceinline__ float chain_walk(const float (*abuf)[NC], const float (*bbuf)[NC],
-                                            float (*rbuf)[NC], int col, float sl, bool first,
+__device__ __forceinline__ float chain_walk(const float2 (*abuf)[NC], const float (*bbuf)[NC],
+                                            float (*ybuf)[NC], int col, float sl, bool first,
                                             int n) {
   constexpr int H = chain_half<64 / NC>(M);
   float bv[M];
@@ -434,15 +430,16 @@ __device__ __forceinline__ float chain_walk(const float (*abuf)[NC], const float
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
       const int m0 = h ? H : 0, m1 = h ? M : H;
-      float av[HM];
+      float2 av[HM];
 #pragma unroll
       for (int m = m0; m < m1; ++m) av[m - m0] = abuf[h * HM + m - m0][col];
 #pragma unroll
       for (int m = m0; m < m1; ++m) {
         float rr = chain_r(sl);
         if (m == 0) rr = first ? 0.f : rr;
-        rbuf[h * HM + m - m0][col] = rr;  // lanes of one column write the same value
-        sl = fmaf(-bv[m], rr, av[m - m0]);
+        const float yv = av[m - m0].x - rr;
+        ybuf[h * HM + m - m0][col] = yv;  // lanes of one column write the same value
+        sl = fmaf(bv[m], yv, av[m - m0].y);
       }
       chain_block_sync();
     }
@@ -459,9 +456,9 @@ __global__ __launch_bounds__(64 * (1 + (ML1 + 64 / NC - 1) / (64 / NC))) void k_
     float* __restrict__ prev, int M, int L, int SL, int BD, int D, int t0, int t1,
     int tile_last) {
   constexpr int W = kChainBlockW, LPW = 64 / NC, XA = kChainXAhead;
-  __shared__ float abuf[2 * HM][NC];  // A of the next position, by half and layer in it
-  __shared__ float bbuf[2 * HM][NC];  // B
-  __shared__ float rbuf[2 * HM][NC];  // r of the position taken last
+  __shared__ float2 abuf[2 * HM][NC];  // x + 1/2 and A of the next position, by half and layer in it
+  __shared__ float bbuf[2 * HM][NC];   // B
+  __shared__ float ybuf[2 * HM][NC];   // y of the position taken last
   const int lane = (int)threadIdx.x & 63;
   const int wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
   const int col = lane & (NC - 1);
@@ -477,7 +474,7 @@ __global__ __launch_bounds__(64 * (1 + (ML1 + 64 / NC - 1) / (64 / NC))) void k_
     chain_block_sync();
     auto walk = [&](auto mc) {
       constexpr int MM = ML0 + decltype(mc)::value;
-      if (M == MM) sl = chain_walk<MM, NC, HM>(abuf, bbuf, rbuf, col, sl, t0 == 0, r1 - r0);
+      if (M == MM) sl = chain_walk<MM, NC, HM>(abuf, bbuf, ybuf, col, sl, t0 == 0, r1 - r0);
     };
     static_for<ML1 - ML0 + 1>(walk);
     if (lane < NC && live) prev[c] = sl;
@@ -505,11 +502,10 @@ __global__ __launch_bounds__(64 * (1 + (ML1 + 64 / NC - 1) / (64 / NC))) void k_
 #pragma unroll
   for (int k = 0; k < XA; ++k) xq[k] = next_x();
   chain_block_load(Sc, Hf + (size_t)mc * L * D + d, rs, D, L, b, v, hh, h0);
-  float xh = 0.f, part = 0.f;
-  // A of position r (its accumulator v[r] complete)
+  float part = 0.f;
+  // what wave 0 needs of position t, its accumulator complete
   auto prepare = [&](int t, float acc, float xv) {
-    xh = chain_xh(xv, mc == 0 && t == 0);
-    if (has) abuf[slot][col] = chain_a(h0, xh, acc);
+    if (has) abuf[slot][col] = make_float2(chain_xh(xv, mc == 0 && t == 0), chain_scaled(acc));
   };
   auto tile_of = [&](int r) { return r + 1 < W && b + r + 1 < L && (r + 1 < r1 || tile_last); };
   auto begin = [&](auto rc) {
@@ -519,7 +515,7 @@ __global__ __launch_bounds__(64 * (1 + (ML1 + 64 / NC - 1) / (64 / NC))) void k_
     part = chain_block_first_part<r>(v, hh);
   };
   static_for<W>(begin);
-  if (has) bbuf[slot][col] = chain_b(h0);
+  if (has) bbuf[slot][col] = chain_scaled(h0);
   chain_block_sync();
   chain_block_sync();
   if (half) chain_block_sync();
@@ -527,7 +523,7 @@ __global__ __launch_bounds__(64 * (1 + (ML1 + 64 / NC - 1) / (64 / NC))) void k_
     constexpr int r = decltype(rc)::value;
     if (r < r0 || r >= r1) return;
     const int t = b + r;
-    const float yv = xh - rbuf[slot][col];
+    const float yv = ybuf[slot][col];
     const float zv = fmaf(h0, yv, v[r]);
     v[r] = yv;
     if constexpr (r + 1 < W) {
