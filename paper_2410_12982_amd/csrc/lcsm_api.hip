@@ -343,7 +343,8 @@ hipError_t launch_tile(lcsm_ctx* c, int i, int U, int dst_len) {
   const bool boundary = t0 && i % t0 == 0;
   hipError_t e = hipSuccess;
   if (boundary) {
-    e = lcsm::launch_cm_yin(c->S, c->C, c->s, c->ly.cm, c->mirrored, i, c->stream);
+    e = lcsm::launch_cm_yin(lcsm::state_rows(c->S, c->s), c->C, c->s, c->ly.cm, c->mirrored, i,
+                            c->stream);
     c->mirrored = i;
   }
   if (e != hipSuccess) return e;
@@ -357,8 +358,53 @@ hipError_t launch_tile(lcsm_ctx* c, int i, int U, int dst_len) {
   }
   if (e == hipSuccess && boundary && ((unsigned)i & c->ly.cm_mask)) {
     const int r1 = i + t0 < c->s.L ? i + t0 : c->s.L;
-    e = lcsm::launch_cm_merge(c->C, c->S, c->s, c->ly.cm, i, r1, c->ly.cm_store, c->stream);
+    e = lcsm::launch_cm_merge(c->C, lcsm::state_rows(c->S, c->s), c->s, c->ly.cm, i, r1,
+                              c->ly.cm_store, c->stream);
   }
+  return e;
+}
+
+// The prompt of a mirrored tile size on the mirror.  Its inputs go there
+// straight (the state's rows are read again only by tiles above the mirrored
+// sizes); its outputs are the tile i = P with the spectra of the filters' first
+// P taps delayed by P, left in C rows [P, 2P) and copied out; the ordinary tile
+// of i = P then stores over them.  The delayed spectra are made in the scratch,
+// as many layers at a time as fit with their transposed taps (prompt_layers,
+// none: the general path, whose tile goes through the state).  18 layers x 3072
+// columns, P = 8192: 5.9 ms against 11.7 by the general path.
+int prompt_layers(const lcsm_ctx* c, int P) {
+  const size_t per = (sizeof(float2) * (size_t)(P + 1) + sizeof(float) * (size_t)P) * c->s.D;
+  const size_t n = (c->ly.scratch_bytes - (c->ly.scratch_bytes ? 256 : 0)) / per;
+  // the split tile's odd half takes the taps' place: one pair at least
+  if (2 * P > lcsm::kMaxColFftN1 && n * c->s.D < 2) return 0;
+  return n < (size_t)c->s.M ? (int)n : c->s.M;
+}
+
+hipError_t prefill_mirrored(lcsm_ctx* c, int P, int nl, const float* y, size_t y_stride, float* z,
+                            size_t z_stride) {
+  const Shape& s = c->s;
+  const lcsm::CmShape& cm = c->ly.cm;
+  const lcsm::Rows in{const_cast<float*>(y), (size_t)s.BD, y_stride};
+  hipError_t e = hipSuccess;
+  if (!c->ly.cm_store) e = lcsm::launch_rows_in(y, y_stride, c->S, s, P, c->stream);
+  if (e == hipSuccess) e = lcsm::launch_cm_yin(in, c->C, s, cm, 0, P, c->stream);
+  c->mirrored = P;
+  const size_t hbytes = align_up(sizeof(float2) * (size_t)(P + 1) * s.D * nl);
+  float2* H = c->scratch;
+  float* X = (float*)((char*)c->scratch + hbytes);
+  for (int m0 = 0; e == hipSuccess && m0 < s.M; m0 += nl) {
+    Shape sl = s;
+    sl.M = s.M - m0 < nl ? s.M - m0 : nl;
+    e = lcsm::launch_prompt_spectra(c->Hf, H, c->tw, s, m0, sl.M, P, X, c->stream);
+    if (e == hipSuccess)
+      e = lcsm::launch_cm_tile(c->C + (size_t)m0 * cm.PC * s.L, H, c->tw, sl, cm, P, P, P, true,
+                               (float2*)X, c->ly.scratch_bytes - hbytes, c->stream);
+  }
+  // row P + t of the mirror to position t of z: z moved back by P positions
+  const lcsm::Rows out{(float*)((uintptr_t)z - sizeof(float) * z_stride * (size_t)P), (size_t)s.BD,
+                       z_stride};
+  if (e == hipSuccess) e = lcsm::launch_cm_merge(c->C, out, s, cm, P, 2 * P, true, c->stream);
+  if (e == hipSuccess) e = launch_tile(c, P, P, P);
   return e;
 }
 
@@ -817,6 +863,13 @@ int lcsm_prefill(lcsm_ctx* c, int P, const float* y, size_t y_stride, float* z, 
   // a prompt of a direct tile size: P ordinary steps
   if (tile_kind(c->opt, s, P) == LCSM_TILE_DIRECT) return lcsm_run(c, P, y, y_stride, z, z_stride);
   // P is an FFT tile size, so its cached spectra and the twiddles for 2P exist
+  const int nl = tile_kind(c->opt, s, P) == LCSM_TILE_FFT_CM ? prompt_layers(c, P) : 0;
+  if (nl > 0) {
+    const hipError_t em = prefill_mirrored(c, P, nl, y, y_stride, z, z_stride);
+    if (em != hipSuccess) return fail(c, LCSM_EDEVICE, "prefill", em);
+    c->t = P;
+    return LCSM_OK;
+  }
   // the prompt into state rows [0, P)
   hipError_t e = lcsm::launch_rows_in(y, y_stride, c->S, s, P, c->stream);
   // rows [P, 2P) are clear after a reset unless a mirror's merges store (then

@@ -463,8 +463,11 @@ __device__ __forceinline__ int cm_pair_of(int r, bool bpair, int PC, int D) {
 constexpr int kCmT = 64;  // transpose tile: 64 pairs x 64 positions
 
 // C[m][p][t] = (S[m][t][a], S[m][t][b]) for t in [row0, row1).  Grid (pair
-// blocks, position blocks, M); 256 threads.
+// blocks, position blocks, M); 256 threads.  Here and in the copies below a
+// layer of S is lstride floats and a position's row rstride floats from the
+// next, so that the prompt's inputs and outputs [t][m][c] are copied as well.
 __global__ __launch_bounds__(kTThreads) void k_cm_yin(const float* __restrict__ S, size_t lstride,
+                                                      size_t rstride,
                                                       float2* __restrict__ C, size_t cstride,
                                                       int L, int PC, int BD, int D, int bpair,
                                                       int row0, int row1) {
@@ -481,7 +484,7 @@ __global__ __launch_bounds__(kTThreads) void k_cm_yin(const float* __restrict__ 
     for (int k = 0; k < kCmT / 4; ++k) {
       const int r = y4 + 4 * k, t = r0 + r;
       if (p < PC && t < row1) {
-        const float* row = Sm + (size_t)t * BD;
+        const float* row = Sm + (size_t)t * rstride;
         tile[r][x] = make_float2(row[a], b >= 0 ? row[b] : 0.f);
       }
     }
@@ -501,7 +504,8 @@ __global__ __launch_bounds__(kTThreads) void k_cm_yin(const float* __restrict__ 
 template <bool STORE>
 __global__ __launch_bounds__(kTThreads) void k_cm_merge(const float2* __restrict__ C,
                                                         size_t cstride, float* __restrict__ S,
-                                                        size_t lstride, int L, int PC, int BD,
+                                                        size_t lstride, size_t rstride, int L,
+                                                        int PC, int BD,
                                                         int D, int bpair, int row0, int row1) {
   __shared__ float2 tile[kCmT][kCmT + 1];
   const int m = (int)blockIdx.z;
@@ -523,7 +527,7 @@ __global__ __launch_bounds__(kTThreads) void k_cm_merge(const float2* __restrict
   for (int k = 0; k < kCmT / 4; ++k) {
     const int r = y4 + 4 * k, t = r0 + r;
     if (t < row1) {
-      float* row = Sm + (size_t)t * BD;
+      float* row = Sm + (size_t)t * rstride;
       const float2 v = tile[r][x];
       row[a] = STORE ? v.x : row[a] + v.x;
       if (b >= 0) row[b] = STORE ? v.y : row[b] + v.y;
@@ -599,6 +603,7 @@ __device__ __forceinline__ void cm_store4(float* row, int a0, int b0, int g, con
 // four pairs of rows r, r+16, r+32, r+48; phase 2: each group of 32 lanes
 // writes the 64 positions of one pair as 32 float4 (two positions each).
 __global__ __launch_bounds__(kTThreads) void k_cm_yin4(const float* __restrict__ S, size_t lstride,
+                                                       size_t rstride,
                                                        float2* __restrict__ C, size_t cstride,
                                                        int L, int BD, int D, int bpair, int row0,
                                                        int row1) {
@@ -615,7 +620,7 @@ __global__ __launch_bounds__(kTThreads) void k_cm_yin4(const float* __restrict__
       const int r = r16 + 16 * k;
       if (r0 + r < row1) {
         float2 v[4];
-        cm_load4(Sm + (size_t)(r0 + r) * BD, a0, b0, g, v);
+        cm_load4(Sm + (size_t)(r0 + r) * rstride, a0, b0, g, v);
 #pragma unroll
         for (int j = 0; j < 4; ++j) tile[r][4 * g + j] = v[j];
       }
@@ -640,7 +645,8 @@ __global__ __launch_bounds__(kTThreads) void k_cm_yin4(const float* __restrict__
 template <bool STORE>
 __global__ __launch_bounds__(kTThreads) void k_cm_merge4(const float2* __restrict__ C,
                                                          size_t cstride, float* __restrict__ S,
-                                                         size_t lstride, int L, int BD, int D,
+                                                         size_t lstride, size_t rstride, int L,
+                                                         int BD, int D,
                                                          int bpair, int row0, int row1) {
   __shared__ float2 tile[kCmT][kCmT + 1];
   const int m = (int)blockIdx.z;
@@ -672,7 +678,7 @@ __global__ __launch_bounds__(kTThreads) void k_cm_merge4(const float2* __restric
       float2 v[4];
 #pragma unroll
       for (int j = 0; j < 4; ++j) v[j] = tile[r][4 * g + j];
-      cm_store4<STORE>(Sm + (size_t)(r0 + r) * BD, a0, b0, g, v);
+      cm_store4<STORE>(Sm + (size_t)(r0 + r) * rstride, a0, b0, g, v);
     }
   }
 }
@@ -838,6 +844,79 @@ __global__ __launch_bounds__(ColCfg<NS>::NT, ColCfg<NS>::MINB) void k_cm_tile2(
   });
 }
 
+// Spectra of the filters' first P taps, delayed by P, for the prompt's own
+// outputs: Hc[g][k] = (-1)^k DFT_2P(h_g[0, P))[k] / 2P for the columns g = m D
+// + d of X[g][r] = h[m, d, r] (r < P, contiguous; the delay by half the length
+// is the sign).  One pair of columns per workgroup, the second absent at an
+// odd end: z = h_a + i h_b, Ha = (Z[k] + conj Z[2P-k]) / 2, Hb = (Z[k] -
+// conj Z[2P-k]) / 2i.  Contiguous reads and writes; the general path (four-step
+// over the lag-major taps) took 1.9 ms for 13824 filters at 2P = 16384, this
+// one with its transpose 0.57 ms.
+template <int N>
+__global__ __launch_bounds__(ColCfg<N>::NT, ColCfg<N>::MINB) void k_prompt_spectra(
+    const float* __restrict__ X, float2* __restrict__ Hc, const float2* __restrict__ tw,
+    int ncols) {
+  constexpr int NT = ColCfg<N>::NT, U = N / 2, SH = ColCfg<N>::SH;
+  using TW = typename std::conditional<ColCfg<N>::TWL, fft::TwLds<N>, TwSplit<N>>::type;
+  __shared__ float2 buf[ColCfg<N>::SLOTS];
+  __shared__ float2 twl[ColCfg<N>::TWL ? N : N / 64 + 64];
+  TW twz;
+  if constexpr (ColCfg<N>::TWL) {
+    fft::load_twiddles<N, NT>(twl, tw);
+    twz = TW{twl};
+  } else {
+    for (int j = (int)threadIdx.x; j < N / 64; j += NT) twl[j] = tw[N + 64 * j];
+    for (int l = (int)threadIdx.x; l < 64; l += NT) twl[N / 64 + l] = tw[N + l];
+    twz = TW{twl, twl + N / 64};
+  }
+  const int g = 2 * (int)blockIdx.x;
+  const bool hasb = g + 1 < ncols;
+  const float* xa = X + (size_t)g * U;
+  fft::forward_from_global<N, 1, 1, NT, true, SH>(buf, twz, [&](int row, int) {
+    return make_float2(xa[row], hasb ? xa[U + row] : 0.f);
+  });
+  float2* ha = Hc + (size_t)g * (U + 1);
+  for (int k = (int)threadIdx.x; k <= U; k += NT) {
+    const float s = (k & 1 ? -0.5f : 0.5f) / (float)N;
+    const float2 a = buf[fft::lds_slot<SH>(k)], b = buf[fft::lds_slot<SH>((N - k) & (N - 1))];
+    ha[k] = make_float2(s * (a.x + b.x), s * (a.y - b.y));
+    if (hasb) ha[U + 1 + k] = make_float2(s * (a.y + b.y), -s * (a.x - b.x));
+  }
+}
+
+// The same for 2P = 2 NS: the even (PAR = 0) and odd bins k = 2 kk + PAR <= NS
+// as an NS-point transform (see k_fft_coltile2); the mirror of bin kk is kk' =
+// (NS - kk - PAR) mod NS of the same half.
+template <int NS, int PAR>
+__global__ __launch_bounds__(ColCfg<NS>::NT, ColCfg<NS>::MINB) void k_prompt_spectra2(
+    const float* __restrict__ X, float2* __restrict__ Hc, const float2* __restrict__ tw,
+    int ncols) {
+  constexpr int NT = ColCfg<NS>::NT, U = NS, N = 2 * NS, SH = ColCfg<NS>::SH;
+  __shared__ float2 buf[ColCfg<NS>::SLOTS];
+  __shared__ float2 twl[NS / 64 + 64];
+  for (int j = (int)threadIdx.x; j < NS / 64; j += NT) twl[j] = tw[NS + 64 * j];
+  for (int l = (int)threadIdx.x; l < 64; l += NT) twl[NS / 64 + l] = tw[NS + l];
+  const TwSplit<NS> twz{twl, twl + NS / 64};
+  constexpr int CC = NS / 16;
+  const int g = 2 * (int)blockIdx.x;
+  const bool hasb = g + 1 < ncols;
+  const float* xa = X + (size_t)g * U;
+  fft::forward_from_global<NS, 1, 1, NT, false, SH>(buf, twz, [&](int row, int) -> float2 {
+    const float2 v = make_float2(xa[row], hasb ? xa[U + row] : 0.f);
+    if constexpr (PAR == 1) return cmul(v, cmul(tw[N + (row & (CC - 1))], tw[32 + row / CC]));
+    return v;
+  });
+  float2* ha = Hc + (size_t)g * (U + 1);
+  constexpr float s = (PAR ? -0.5f : 0.5f) / (float)N;
+  for (int kk = (int)threadIdx.x; 2 * kk + PAR <= U; kk += NT) {
+    const int k = 2 * kk + PAR;
+    const float2 a = buf[fft::lds_slot<SH>(kk)];
+    const float2 b = buf[fft::lds_slot<SH>((NS - kk - PAR) & (NS - 1))];
+    ha[k] = make_float2(s * (a.x + b.x), s * (a.y - b.y));
+    if (hasb) ha[U + 1 + k] = make_float2(s * (a.y + b.y), -s * (a.x - b.x));
+  }
+}
+
 }  // namespace
 
 int fft_col_chunk(int U, size_t scratch_bytes, long long total_cols) {
@@ -923,43 +1002,50 @@ hipError_t launch_fft_col_tile(float* S, const float2* Hc, const float2* tw, con
 
 // 16-byte mirror copies: every block of 64 pairs lies in whole aligned runs
 // (and L even keeps the two positions of a float4 in one pair's row).
-static bool cm_vec(const Shape& s, const CmShape& cm) {
-  if (s.L % 2 != 0) return false;
+static bool cm_vec(const Shape& s, const CmShape& cm, const Rows& rows, int row0) {
+  if (s.L % 2 != 0 || row0 % 2 != 0) return false;
+  if (((uintptr_t)rows.p) % 16 != 0 || rows.lstride % 4 != 0 || rows.rstride % 4 != 0) return false;
   return cm.bpair ? s.D % kCmT == 0 : s.BD % (2 * kCmT) == 0;
 }
 
-hipError_t launch_cm_yin(const float* S, float2* C, const Shape& s, const CmShape& cm, int row0,
+hipError_t launch_cm_yin(const Rows& rows, float2* C, const Shape& s, const CmShape& cm, int row0,
                          int row1, hipStream_t st) {
   if (row1 <= row0) return hipSuccess;
   const dim3 grid((unsigned)((cm.PC + kCmT - 1) / kCmT), (unsigned)((row1 - row0 + kCmT - 1) / kCmT),
                   (unsigned)s.M);
-  if (cm_vec(s, cm) && row0 % 2 == 0)
-    hipLaunchKernelGGL(k_cm_yin4, grid, dim3(kTThreads), 0, st, S, (size_t)s.SL * s.BD, C,
+  const float* S = rows.p;
+  if (cm_vec(s, cm, rows, row0))
+    hipLaunchKernelGGL(k_cm_yin4, grid, dim3(kTThreads), 0, st, S, rows.lstride, rows.rstride, C,
                        (size_t)cm.PC * s.L, s.L, s.BD, s.D, cm.bpair, row0, row1);
   else
-    hipLaunchKernelGGL(k_cm_yin, grid, dim3(kTThreads), 0, st, S, (size_t)s.SL * s.BD, C,
+    hipLaunchKernelGGL(k_cm_yin, grid, dim3(kTThreads), 0, st, S, rows.lstride, rows.rstride, C,
                        (size_t)cm.PC * s.L, s.L, cm.PC, s.BD, s.D, cm.bpair, row0, row1);
   return hipGetLastError();
 }
 
-hipError_t launch_cm_merge(const float2* C, float* S, const Shape& s, const CmShape& cm, int row0,
-                           int row1, bool store, hipStream_t st) {
+hipError_t launch_cm_merge(const float2* C, const Rows& rows, const Shape& s, const CmShape& cm,
+                           int row0, int row1, bool store, hipStream_t st) {
   if (row1 <= row0) return hipSuccess;
   const dim3 grid((unsigned)((cm.PC + kCmT - 1) / kCmT), (unsigned)((row1 - row0 + kCmT - 1) / kCmT),
                   (unsigned)s.M);
-  const bool vec = cm_vec(s, cm) && row0 % 2 == 0;
+  const bool vec = cm_vec(s, cm, rows, row0);
+  float* S = rows.p;
+#define LCSM_MERGE4(ST)                                                                          \
+  hipLaunchKernelGGL(k_cm_merge4<ST>, grid, dim3(kTThreads), 0, st, C, (size_t)cm.PC * s.L, S,   \
+                     rows.lstride, rows.rstride, s.L, s.BD, s.D, cm.bpair, row0, row1)
+#define LCSM_MERGE(ST)                                                                           \
+  hipLaunchKernelGGL(k_cm_merge<ST>, grid, dim3(kTThreads), 0, st, C, (size_t)cm.PC * s.L, S,    \
+                     rows.lstride, rows.rstride, s.L, cm.PC, s.BD, s.D, cm.bpair, row0, row1)
   if (vec && store)
-    hipLaunchKernelGGL(k_cm_merge4<true>, grid, dim3(kTThreads), 0, st, C, (size_t)cm.PC * s.L, S,
-                       (size_t)s.SL * s.BD, s.L, s.BD, s.D, cm.bpair, row0, row1);
+    LCSM_MERGE4(true);
   else if (vec)
-    hipLaunchKernelGGL(k_cm_merge4<false>, grid, dim3(kTThreads), 0, st, C, (size_t)cm.PC * s.L, S,
-                       (size_t)s.SL * s.BD, s.L, s.BD, s.D, cm.bpair, row0, row1);
+    LCSM_MERGE4(false);
   else if (store)
-    hipLaunchKernelGGL(k_cm_merge<true>, grid, dim3(kTThreads), 0, st, C, (size_t)cm.PC * s.L, S,
-                       (size_t)s.SL * s.BD, s.L, cm.PC, s.BD, s.D, cm.bpair, row0, row1);
+    LCSM_MERGE(true);
   else
-    hipLaunchKernelGGL(k_cm_merge<false>, grid, dim3(kTThreads), 0, st, C, (size_t)cm.PC * s.L, S,
-                       (size_t)s.SL * s.BD, s.L, cm.PC, s.BD, s.D, cm.bpair, row0, row1);
+    LCSM_MERGE(false);
+#undef LCSM_MERGE4
+#undef LCSM_MERGE
   return hipGetLastError();
 }
 
@@ -1004,6 +1090,40 @@ hipError_t launch_cm_tile(float2* C, const float2* Hc, const float2* tw, const S
     if (e != hipSuccess) return e;
   }
   return hipSuccess;
+}
+
+hipError_t launch_prompt_spectra(const float* Hf, float2* Hc, const float2* tw, const Shape& s,
+                                 int m0, int nm, int P, float* X, hipStream_t st) {
+  const int nc = nm * s.D, N = 2 * P;
+  const size_t lstride = (size_t)s.L * s.D;
+  const dim3 tin((unsigned)((nc + kTT - 1) / kTT), (unsigned)((P + kTT - 1) / kTT));
+  // columns m D + d of the chunk's layers, taps [0, P) of each, contiguous
+  if (s.D % 4 == 0 && P % 4 == 0)
+    hipLaunchKernelGGL(k_rows_to_cols4, tin, dim3(kTThreads), 0, st, Hf, lstride, s.D, 0, P,
+                       (long long)m0 * s.D, nc, X, P);
+  else
+    hipLaunchKernelGGL(k_rows_to_cols, tin, dim3(kTThreads), 0, st, Hf, lstride, s.D, 0, P,
+                       (long long)m0 * s.D, nc, X, P);
+  const dim3 grid((unsigned)((nc + 1) / 2));
+  switch (N) {
+#define LCSM_PS_CASE(NN)                                                                         \
+  case NN:                                                                                       \
+    hipLaunchKernelGGL(k_prompt_spectra<NN>, grid, dim3(ColCfg<NN>::NT), 0, st, X, Hc, tw, nc);  \
+    break;
+    LCSM_PS_CASE(4) LCSM_PS_CASE(8) LCSM_PS_CASE(16) LCSM_PS_CASE(32) LCSM_PS_CASE(64)
+    LCSM_PS_CASE(128) LCSM_PS_CASE(256) LCSM_PS_CASE(512) LCSM_PS_CASE(1024)
+    LCSM_PS_CASE(2048) LCSM_PS_CASE(4096) LCSM_PS_CASE(8192) LCSM_PS_CASE(16384)
+#undef LCSM_PS_CASE
+    case 2 * kMaxColFftN1:
+      hipLaunchKernelGGL((k_prompt_spectra2<kMaxColFftN1, 0>), grid, dim3(ColCfg<kMaxColFftN1>::NT),
+                         0, st, X, Hc, tw, nc);
+      hipLaunchKernelGGL((k_prompt_spectra2<kMaxColFftN1, 1>), grid, dim3(ColCfg<kMaxColFftN1>::NT),
+                         0, st, X, Hc, tw, nc);
+      break;
+    default:
+      return hipErrorInvalidValue;
+  }
+  return hipGetLastError();
 }
 
 }  // namespace lcsm

@@ -171,14 +171,28 @@ struct CmShape {
   int bpair;  // 1: batch pairs, 0: neighbouring columns
 };
 
-// C[m][p][t] = (S[m][t][a], S[m][t][b]) for positions t in [row0, row1).
-hipError_t launch_cm_yin(const float* S, float2* C, const Shape& s, const CmShape& cm, int row0,
+// Rows by position of every layer: row t of layer m at p + m lstride + t
+// rstride (floats).  The state, or a prompt's inputs and outputs.
+struct Rows {
+  float* p;
+  size_t lstride, rstride;
+};
+inline Rows state_rows(float* S, const Shape& s) { return {S, (size_t)s.SL * s.BD, (size_t)s.BD}; }
+
+// C[m][p][t] = (row t of layer m)[a], [b] for positions t in [row0, row1).
+hipError_t launch_cm_yin(const Rows& rows, float2* C, const Shape& s, const CmShape& cm, int row0,
                          int row1, hipStream_t st);
 
-// State rows t in [row0, row1) receive the mirrored accumulators C[m][p][t]:
+// Rows t in [row0, row1) receive the mirrored accumulators C[m][p][t]:
 // stored (the rows hold nothing else yet) or added.
-hipError_t launch_cm_merge(const float2* C, float* S, const Shape& s, const CmShape& cm, int row0,
-                           int row1, bool store, hipStream_t st);
+hipError_t launch_cm_merge(const float2* C, const Rows& rows, const Shape& s, const CmShape& cm,
+                           int row0, int row1, bool store, hipStream_t st);
+
+// Channel-major spectra Hc[(m - m0) D + d][k], k <= P, of tile size P of the
+// filters of layers [m0, m0 + nm) cut to their first P taps and delayed by P.
+// X: nm D P floats of scratch.  2P <= kMaxColFftN.
+hipError_t launch_prompt_spectra(const float* Hf, float2* Hc, const float2* tw, const Shape& s,
+                                 int m0, int nm, int P, float* X, hipStream_t st);
 
 // FFT gray tile of side U at position i on the mirror, all layers: inputs
 // C[p][i-U, i), outputs j < dst_len into C[p][i+j] (stored when `store`, else

@@ -133,3 +133,49 @@ def test_prefill_errors():
     ctx.reset()
     ctx.prefill(y[:128], z[:128])
     assert ctx.position == 128
+
+
+@pytest.mark.parametrize("case", [
+    # (M, B, D, L, P, options, extra floats per position slab, first slab moved by floats)
+    (3, 2, 64, 512, 64, {}, 0, 0),            # 16-byte copies, pairs of batch rows
+    (3, 2, 64, 512, 64, {}, 4, 0),
+    (3, 2, 64, 512, 64, {}, 2, 0),            # slabs that are not 16-byte apart
+    (3, 2, 64, 512, 64, {}, 0, 1),            # nor aligned
+    (2, 3, 37, 500, 32, {}, 1, 0),            # neighbouring columns, the last one alone
+    (2, 1, 128, 300, 2, {}, 0, 0),            # the smallest mirrored prompt
+    (5, 1, 33, 4100, 2048, {"scratch_mib": 2}, 0, 0),  # two layers' spectra at a time
+    (1, 1, 1, 1024, 256, {}, 0, 0),           # one column: the spectra do not fit the scratch
+    (1, 2, 6, 32768, 16384, {}, 0, 0),        # the prompt's transform as two halves
+    (1, 2, 4, 70000, 1024, {}, 0, 0),         # larger tiles read the prompt from the state
+])
+def test_prefill_on_the_mirror(case):
+    """The prompt of a mirrored tile size (mirror forced from 2U = 4): inputs
+    straight into the mirror, delayed spectra by chunks of layers, outputs
+    straight out of it; then the generation goes on."""
+    M, B, D, L, P, opts, pad, move = case
+    say(f"[prefill mirror] {case}")
+    w = datagen.Workload("prefill_cm", M, B, D, L, decay=max(L / 8, 8.0), seed=7 + P)
+    ctx, _ = make_ctx(w, options={"direct_max_u": 1, "col_fft_min_n": 4, **opts})
+    n = min(L, 2 * P + 70) if L < 70000 else L
+    y = datagen.y_torch(w, dev())[:n].contiguous()
+    slab = M * B * D
+    ys = torch.zeros(P * (slab + pad) + move, device=dev())
+    zs = torch.full_like(ys, float("nan"))
+    rows = ys[move:].view(P, slab + pad)
+    rows[:, :slab] = y[:P].reshape(P, slab)
+    z = torch.full_like(y, float("nan"))
+    r = lcsm_mod().raw().lcsm_prefill(ctx._ctx, P, ys.data_ptr() + 4 * move, slab + pad,
+                                      zs.data_ptr() + 4 * move, slab + pad)
+    assert r == 0
+    ctx.run(y[P:], z[P:])
+    torch.cuda.synchronize()
+    out = zs[move:].view(P, slab + pad)
+    assert torch.isnan(out[:, slab:]).all()  # nothing written between the slabs
+    z[:P] = out[:, :slab].reshape(P, M, B, D)
+    h = filters_to_columns(datagen.filters_np(w), B)[:n]
+    zr = conv.causal_conv_fft(y.cpu().numpy().reshape(n, -1).astype(np.float64), h.reshape(n, -1))
+    err = rel_err(z.cpu().numpy().reshape(n, -1), zr)
+    say(f"  rel err {err:.3e}")
+    # sums over at most 16 levels of tiles, each within about 10 roundings of its 2U-point transforms
+    assert err <= 16 * 10 * 2.0 ** -24
+    ctx.close()
