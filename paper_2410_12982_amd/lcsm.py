@@ -132,6 +132,7 @@ for _name, (_res, _args) in _SIGS.items():
     _fn.argtypes = _args
 
 EXPORTED = tuple(_SIGS)
+_lcsm_step, _lcsm_step_chain = _lib.lcsm_step, _lib.lcsm_step_chain
 
 
 class LcsmError(RuntimeError):
@@ -185,10 +186,44 @@ def _after_current(stream, device):
     """Order work queued next on ``stream`` after everything already queued on
     torch's current stream (where callers produce filters and inputs), when
     the two differ: the library's calls are asynchronous on their own stream."""
-    import torch
     cur = torch.cuda.current_stream(device)
     if cur.cuda_stream != stream.cuda_stream:
         stream.wait_stream(cur)
+
+
+# What a call per position costs on the host is mostly Python around a launch
+# of about 2 us, so the per-position calls below look the current stream up by
+# its handle (no stream object is made: 0.1 against 1.3 us), hold the handles
+# that do not change and check a slab in one expression: 8.5 -> 6.2 us per
+# ``Lcsm.step`` of a small context.
+_current_raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+if _current_raw is None:
+    def _current_raw(index):
+        return torch.cuda.current_stream(index).cuda_stream
+
+_F32 = torch.float32
+
+
+class _Order:
+    """The stream of a context, to be called before work is queued on it:
+    ``_after_current`` when another stream is current."""
+    __slots__ = ("stream", "device", "index", "raw")
+
+    def __init__(self, stream, device):
+        self.stream, self.device = stream, torch.device(device)
+        self.raw = stream.cuda_stream
+        self.index = self.device.index
+
+    def __call__(self):
+        if self.index is None or _current_raw(self.index) != self.raw:
+            _after_current(self.stream, self.device)
+
+
+def _slab_ptr(tensor, shape, name):
+    """Address of a contiguous CUDA fp32 tensor of this shape (a tuple)."""
+    if tensor.dtype is _F32 and tensor.shape == shape and tensor.is_cuda and tensor.is_contiguous():
+        return tensor.data_ptr()
+    raise ValueError(f"{name} must be a contiguous CUDA fp32 tensor of shape {shape}")
 
 
 class Lcsm:
@@ -215,10 +250,12 @@ class Lcsm:
             options = o
         self._opts_obj = options
         self.stream = stream if stream is not None else torch.cuda.current_stream(self.device)
+        self._order = _Order(self.stream, self.device)
+        self._shape = (self.M, self.B, self.D)
         nbytes = workspace_bytes(self.M, self.B, self.D, self.L, options)
         self.workspace = torch.empty(nbytes, dtype=torch.uint8, device=self.device)
         self._ctx = _vp()
-        _after_current(self.stream, self.device)
+        self._order()
         r = _lib.lcsm_init(ctypes.byref(self._ctx), filters.data_ptr(), self.M, self.B, self.D,
                            self.L, self.stream.cuda_stream, self.workspace.data_ptr(), nbytes,
                            _opts(options))
@@ -234,41 +271,39 @@ class Lcsm:
             raise LcsmError(r, where, detail)
 
     def _slab(self, tensor, shape, name):
-        import torch
-        if not (tensor.is_cuda and tensor.dtype == torch.float32 and tensor.is_contiguous()
-                and tuple(tensor.shape) == shape and tensor.device == self.device):
-            raise ValueError(f"{name} must be a contiguous CUDA fp32 tensor of shape {shape}")
-        return tensor.data_ptr()
+        if (tensor.dtype is _F32 and tensor.shape == shape and tensor.device == self.device
+                and tensor.is_contiguous()):
+            return tensor.data_ptr()
+        raise ValueError(f"{name} must be a contiguous CUDA fp32 tensor of shape {shape}")
 
     # -- ABI calls
     def step(self, y_t, z_t=None):
         """Emit z_t for all layers given y_t [M, B, D]; queues the gray tile."""
-        import torch
-        shape = (self.M, self.B, self.D)
+        shape = self._shape
         if z_t is None:
             z_t = torch.empty(shape, dtype=torch.float32, device=self.device)
-        _after_current(self.stream, self.device)
-        self._check(_lib.lcsm_step(self._ctx, self._slab(y_t, shape, "y_t"),
-                                   self._slab(z_t, shape, "z_t")), "lcsm_step")
+        self._order()
+        r = _lcsm_step(self._ctx, self._slab(y_t, shape, "y_t"), self._slab(z_t, shape, "z_t"))
+        if r:
+            self._check(r, "lcsm_step")
         return z_t
 
     def step_chain(self, x_t, z_t=None):
         """One position with the built-in tanh chain; x_t [M, B, D]."""
-        import torch
-        shape = (self.M, self.B, self.D)
+        shape = self._shape
         if z_t is None:
             z_t = torch.empty(shape, dtype=torch.float32, device=self.device)
-        _after_current(self.stream, self.device)
-        self._check(_lib.lcsm_step_chain(self._ctx, self._slab(x_t, shape, "x_t"),
-                                         self._slab(z_t, shape, "z_t")), "lcsm_step_chain")
+        self._order()
+        r = _lcsm_step_chain(self._ctx, self._slab(x_t, shape, "x_t"), self._slab(z_t, shape, "z_t"))
+        if r:
+            self._check(r, "lcsm_step_chain")
         return z_t
 
     def step_layer(self, layer, y, z=None):
-        import torch
         shape = (self.B, self.D)
         if z is None:
             z = torch.empty(shape, dtype=torch.float32, device=self.device)
-        _after_current(self.stream, self.device)
+        self._order()
         self._check(_lib.lcsm_step_layer(self._ctx, int(layer), self._slab(y, shape, "y"),
                                          self._slab(z, shape, "z")), "lcsm_step_layer")
         return z
@@ -462,6 +497,7 @@ class Base:
         self.B = int(B)
         self.device = filters.device
         self.stream = stream if stream is not None else torch.cuda.current_stream(self.device)
+        self._order = _Order(self.stream, self.device)
         nbytes = base_workspace_bytes(self.kind, self.M, self.B, self.D, self.L)
         self.workspace = torch.empty(nbytes, dtype=torch.uint8, device=self.device)
         self._ctx = _vp()
@@ -479,16 +515,13 @@ class Base:
             raise LcsmError(r, where, detail)
 
     def step(self, y_t, z_t=None):
-        import torch
         shape = (self.M, self.B, self.D)
         if z_t is None:
             z_t = torch.empty(shape, dtype=torch.float32, device=self.device)
-        for t, name in ((y_t, "y_t"), (z_t, "z_t")):
-            if not (t.is_cuda and t.dtype == torch.float32 and t.is_contiguous()
-                    and tuple(t.shape) == shape):
-                raise ValueError(f"{name} must be a contiguous CUDA fp32 tensor of shape {shape}")
-        _after_current(self.stream, self.device)
-        self._check(_lib.lcsm_base_step(self._ctx, y_t.data_ptr(), z_t.data_ptr()), "lcsm_base_step")
+        self._order()
+        r = _lib.lcsm_base_step(self._ctx, _slab_ptr(y_t, shape, "y_t"), _slab_ptr(z_t, shape, "z_t"))
+        if r:
+            self._check(r, "lcsm_base_step")
         return z_t
 
     def reset(self):
@@ -536,6 +569,7 @@ class Dd:
                 setattr(o, k, int(v))
             options = o
         self.stream = stream if stream is not None else torch.cuda.current_stream(self.device)
+        self._order = _Order(self.stream, self.device)
         nbytes = dd_workspace_bytes(self.M, self.B, self.D, self.L, options)
         self.workspace = torch.empty(nbytes, dtype=torch.uint8, device=self.device)
         self._ctx = _vp()
@@ -552,17 +586,14 @@ class Dd:
             raise LcsmError(r, where, detail)
 
     def step(self, y_t, rho_t, z_t=None):
-        import torch
         shape = (self.M, self.B, self.D)
         if z_t is None:
             z_t = torch.empty(shape, dtype=torch.float32, device=self.device)
-        for t, name in ((y_t, "y_t"), (rho_t, "rho_t"), (z_t, "z_t")):
-            if not (t.is_cuda and t.dtype == torch.float32 and t.is_contiguous()
-                    and tuple(t.shape) == shape):
-                raise ValueError(f"{name} must be a contiguous CUDA fp32 tensor of shape {shape}")
-        _after_current(self.stream, self.device)
-        self._check(_lib.lcsm_dd_step(self._ctx, y_t.data_ptr(), rho_t.data_ptr(), z_t.data_ptr()),
-                    "lcsm_dd_step")
+        self._order()
+        r = _lib.lcsm_dd_step(self._ctx, _slab_ptr(y_t, shape, "y_t"), _slab_ptr(rho_t, shape, "rho_t"),
+                              _slab_ptr(z_t, shape, "z_t"))
+        if r:
+            self._check(r, "lcsm_dd_step")
         return z_t
 
     def reset(self):
@@ -616,8 +647,9 @@ class Synth:
                 setattr(o, k, int(v))
             options = o
         self.stream = stream if stream is not None else torch.cuda.current_stream(self.device)
+        self._order = _Order(self.stream, self.device)
         self._ctx = _vp()
-        _after_current(self.stream, self.device)
+        self._order()
         r = _lib.lcsm_synth_init(ctypes.byref(self._ctx), filters.data_ptr(), w_up.data_ptr(),
                                  b_up.data_ptr(), w_down.data_ptr(), b_down.data_ptr(), M, self.B,
                                  D, self.L, self.stream.cuda_stream, _opts(options))
@@ -634,17 +666,13 @@ class Synth:
     def step(self, eps_t, act_t=None):
         """Position t: noise eps_t [B, D] in, block outputs of every layer
         act_t [M, B, D] out (act_t[M-1] is the model's output)."""
-        import torch
         if act_t is None:
             act_t = torch.empty((self.M, self.B, self.D), dtype=torch.float32, device=self.device)
-        for t, shape, name in ((eps_t, (self.B, self.D), "eps_t"),
-                               (act_t, (self.M, self.B, self.D), "act_t")):
-            if not (t.is_cuda and t.dtype == torch.float32 and t.is_contiguous()
-                    and tuple(t.shape) == shape):
-                raise ValueError(f"{name} must be a contiguous CUDA fp32 tensor of shape {shape}")
-        _after_current(self.stream, self.device)
-        self._check(_lib.lcsm_synth_step(self._ctx, eps_t.data_ptr(), act_t.data_ptr()),
-                    "lcsm_synth_step")
+        self._order()
+        r = _lib.lcsm_synth_step(self._ctx, _slab_ptr(eps_t, (self.B, self.D), "eps_t"),
+                                 _slab_ptr(act_t, (self.M, self.B, self.D), "act_t"))
+        if r:
+            self._check(r, "lcsm_synth_step")
         return act_t
 
     def reset(self):
