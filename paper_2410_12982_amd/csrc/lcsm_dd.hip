@@ -35,6 +35,7 @@ constexpr int kThreads = 256;
 constexpr int kDdJ = 16;            // outputs per thread of the direct tile
 constexpr int kDdDefaultDirectMaxU = 32;
 constexpr int kDdFusedMaxU = 8;      // tiles fused with the red cell
+constexpr int kDdWideMaxU = 32;      // the same for rectangles (k_dd_step_wide)
 
 // Contributions of the tile of side U of step t (t + 1 a multiple of U,
 // 2U <= t + 1) to the destination rows t + 1 + j, j < 2U - 1, added into dz
@@ -130,6 +131,63 @@ __global__ __launch_bounds__(kThreads) void k_dd_step(const float* __restrict__ 
   }
 }
 
+// The same for UMAX = 16 and 32, rectangles only (t + 1 > 2 UMAX): the recent
+// rows stay in registers, the fixed rows pass by once, and the sums of all
+// tiles meet before one read-modify-write of the 2 UMAX - 1 destination rows.
+// Bound by these rows (UMAX = 32: 286 floats a column, 5.0 TB/s).  Tiles of 16
+// and 32 on their own read the recent and the destination rows again and their
+// fixed rows once per 16 outputs: the steps of UMAX = 16 and 32 take 52 and 119
+// us at 524288 columns against 86 and 262 in two and three launches, and 512
+// positions of 6144 columns 1.39 against 1.51 ms.
+template <int UMAX>
+__global__ __launch_bounds__(kThreads) void k_dd_step_wide(const float* __restrict__ y,
+                                                           const float* __restrict__ rho,
+                                                           float* __restrict__ z,
+                                                           float* __restrict__ Y,
+                                                           float* __restrict__ R, int L, int BD,
+                                                           int t) {
+  const int c = (int)blockIdx.x * kThreads + (int)threadIdx.x;
+  if (c >= BD) return;
+  const int m = (int)blockIdx.y;
+  const size_t e = (size_t)m * BD + c;
+  float* Ym = Y + (size_t)m * L * BD;
+  float* Rm = R + (size_t)m * L * BD;
+  auto yrow = [&](int row) -> float& { return (Ym + (size_t)row * BD)[c]; };
+  auto rrow = [&](int row) -> float& { return (Rm + (size_t)row * BD)[c]; };
+  const float yt = y[e], rt = rho[e];
+  const float acc = yrow(t), y0 = yrow(0), r0 = rrow(0);
+  float wy[UMAX], wr[UMAX], s[2 * UMAX - 1];
+#pragma unroll
+  for (int i = 0; i < UMAX - 1; ++i) {
+    wy[i] = yrow(t - UMAX + 1 + i);
+    wr[i] = rrow(t - UMAX + 1 + i);
+  }
+  wy[UMAX - 1] = yt;
+  wr[UMAX - 1] = rt;
+#pragma unroll
+  for (int j = 0; j < 2 * UMAX - 1; ++j) s[j] = 0.f;
+#pragma unroll
+  for (int U = 1; U <= UMAX; U *= 2)
+#pragma unroll
+    for (int k = 0; k < U; ++k) {
+      const float fy = yrow(U + k), fr = rrow(U + k);
+#pragma unroll
+      for (int i = 0; i < U; ++i) {
+        s[k + i] = fmaf(fy, wr[UMAX - U + i], s[k + i]);
+        s[k + i] = fmaf(fr, wy[UMAX - U + i], s[k + i]);
+      }
+    }
+  z[e] = fmaf(yt, r0, fmaf(y0, rt, acc));
+  yrow(t) = yt;
+  rrow(t) = rt;
+  float d[2 * UMAX - 1];
+#pragma unroll
+  for (int j = 0; j < 2 * UMAX - 1; ++j) d[j] = yrow(t + 1 + j < L ? t + 1 + j : L - 1);
+#pragma unroll
+  for (int j = 0; j < 2 * UMAX - 1; ++j)
+    if (t + 1 + j < L) yrow(t + 1 + j) = d[j] + s[j];
+}
+
 // Direct parallelogram tile of side U for all layers: thread = (column c,
 // outputs j0 .. j0+J-1, layer m).  The recent-block values needed at fixed
 // index k form a window j0+jj-k that slides down by one per k, so each k
@@ -185,52 +243,41 @@ __global__ __launch_bounds__(kThreads) void k_dd_direct(float* __restrict__ Y,
     if (j0 + jj < dlen) dst[(size_t)jj * rs] += acc[jj];
 }
 
-// The same tile for a side UT known at compile time: every value it reads --
-// the two fixed blocks and the window j0-UT+1 .. j0+J-1 of the two recent
-// blocks -- is loaded before the first product (one memory round trip, rows
-// clamped into range and zero-selected, since a load under a condition would
-// wait for the earlier ones), and the window offsets become register names.
-template <int J, int UT, bool SQ>
-__global__ __launch_bounds__(kThreads) void k_dd_direct_u(float* __restrict__ Y,
+// The square tile for a side UT known at compile time (16 and 32, where the
+// rectangles go with the step): every value it reads -- the block of y and the
+// window j0-UT+1 .. j0+J-1 of the block of rho -- is loaded before the first
+// product (one memory round trip, rows clamped into range and zero-selected,
+// since a load under a condition would wait for the earlier ones), and the
+// window offsets become register names.
+template <int J, int UT>
+__global__ __launch_bounds__(kThreads) void k_dd_square_u(float* __restrict__ Y,
                                                           const float* __restrict__ R, int L,
                                                           int BD, int lo, int d0, int dlen) {
-  constexpr int NW = J + UT - 1;  // window: recent index j0 - UT + 1 + i, i < NW
+  constexpr int NW = J + UT - 1;  // window: block index j0 - UT + 1 + i, i < NW
   const int c = (int)blockIdx.x * kThreads + (int)threadIdx.x;
   const int j0 = (int)blockIdx.y * J;
   const int m = (int)blockIdx.z;
   if (c >= BD || j0 >= dlen) return;
   const size_t rs = (size_t)BD;
   float* ycol = Y + (size_t)m * L * BD + c;
-  const float* rcol = R + (size_t)m * L * BD + c;
-  const float* yR = ycol + (size_t)lo * rs;
-  const float* rR = rcol + (size_t)lo * rs;
+  const float* rR = R + (size_t)m * L * BD + c + (size_t)lo * rs;
   const float* yF = ycol + (size_t)UT * rs;
-  const float* rF = rcol + (size_t)UT * rs;
-  float fy[UT], fr[UT], wy[NW], wr[NW];
+  float fy[UT], wr[NW];
 #pragma unroll
-  for (int k = 0; k < UT; ++k) {
-    fy[k] = yF[(size_t)k * rs];
-    fr[k] = SQ ? 0.f : rF[(size_t)k * rs];
-  }
+  for (int k = 0; k < UT; ++k) fy[k] = yF[(size_t)k * rs];
 #pragma unroll
   for (int i = 0; i < NW; ++i) {
     const int idx = j0 - UT + 1 + i;
     const int cl = idx < 0 ? 0 : (idx >= UT ? UT - 1 : idx);
     const float vr = rR[(size_t)cl * rs];
-    const float vy = SQ ? 0.f : yR[(size_t)cl * rs];
-    const bool in = idx >= 0 && idx < UT;
-    wr[i] = in ? vr : 0.f;
-    wy[i] = in ? vy : 0.f;
+    wr[i] = idx >= 0 && idx < UT ? vr : 0.f;
   }
   float* dst = ycol + (size_t)(d0 + j0) * rs;
 #pragma unroll
   for (int jj = 0; jj < J; ++jj) {
     float a = 0.f;
 #pragma unroll
-    for (int k = 0; k < UT; ++k) {
-      a = fmaf(fy[k], wr[jj - k + UT - 1], a);
-      if constexpr (!SQ) a = fmaf(fr[k], wy[jj - k + UT - 1], a);
-    }
+    for (int k = 0; k < UT; ++k) a = fmaf(fy[k], wr[jj - k + UT - 1], a);
     if (j0 + jj < dlen) dst[(size_t)jj * rs] += a;
   }
 }
@@ -250,28 +297,38 @@ __global__ __launch_bounds__(kThreads) void k_dd_direct_u(float* __restrict__ Y,
 // Launch shape: CW real columns per workgroup (the forward transforms run on
 // CW complex columns, the inverse on CW/2), the LDS buffer N x CW complex;
 // NT threads.
+// From kDdWideMinCols columns 2U = 64 to 256 take panels of 32 columns (128-byte
+// row runs: 57.7 -> 56.4 ms for 2048 positions of 524288 columns); fewer columns
+// need the workgroups.  2U = 1024 takes 8, two workgroups per CU (57.7 -> 57.3).
+constexpr long long kDdWideMinCols = 1LL << 17;
 template <int N>
+constexpr int dd_cw(bool wide) {
+  if (wide && N >= 64 && N <= 256) return 32;
+  return N <= 512 ? 16 : (N <= 2048 ? 8 : (N <= 4096 ? 4 : 2));
+}
+template <int N, bool WIDE>
 struct DdCfg {
-  static constexpr int CW = N <= 1024 ? 16 : (N <= 2048 ? 8 : (N <= 4096 ? 4 : 2));
+  static constexpr int CW = dd_cw<N>(WIDE);
   // at most 512 threads: the spectra held across the second transform need
   // more than the 128 registers a 1024-thread workgroup leaves
-  static constexpr int NT = N <= 64 ? 64 : (N <= 128 ? 128 : (N <= 256 ? 256 : 512));
+  static constexpr int NB = N <= 64 ? 64 : (N <= 128 ? 128 : (N <= 256 ? 256 : 512));
+  static constexpr int NT = CW > 16 ? 2 * NB : NB;
   static constexpr bool TWL = (size_t)N * 8 * (CW + 1) <= 163840;
   static constexpr bool TWH = !TWL && (size_t)N * 8 * CW + (size_t)N * 4 <= 163840;
   static constexpr int TWN = TWL ? N : (TWH ? N / 2 : 1);
 };
 
-template <int N>
+template <int N, bool WIDE>
 using DdTw = typename std::conditional<
-    DdCfg<N>::TWL, fft::TwLds<N>,
-    typename std::conditional<DdCfg<N>::TWH, fft::TwLdsHalf<N>, fft::TwGlobal>::type>::type;
+    DdCfg<N, WIDE>::TWL, fft::TwLds<N>,
+    typename std::conditional<DdCfg<N, WIDE>::TWH, fft::TwLdsHalf<N>, fft::TwGlobal>::type>::type;
 
-template <int N, int NT>
-__device__ __forceinline__ DdTw<N> dd_make_tw(float2* lds, const float2* __restrict__ tw) {
-  if constexpr (DdCfg<N>::TWL) {
+template <int N, bool WIDE, int NT>
+__device__ __forceinline__ DdTw<N, WIDE> dd_make_tw(float2* lds, const float2* __restrict__ tw) {
+  if constexpr (DdCfg<N, WIDE>::TWL) {
     fft::load_twiddles<N, NT>(lds, tw);
     return fft::TwLds<N>{lds};
-  } else if constexpr (DdCfg<N>::TWH) {
+  } else if constexpr (DdCfg<N, WIDE>::TWH) {
     fft::load_twiddles<N, NT, N / 2>(lds, tw);
     return fft::TwLdsHalf<N>{lds};
   } else {
@@ -300,21 +357,21 @@ __device__ __forceinline__ void unpack(float2 xk, float2 xnk, float2& a, float2&
 // the plain tile (fo = U).
 // Threads of a workgroup: the block-split form keeps a third spectrum (the
 // running sum) in registers, so from N = 2048 on it takes 1024 threads.
-template <int N, bool MB>
+template <int N, bool MB, bool WIDE>
 constexpr int dd_threads() {
-  return MB && N >= 2048 ? 1024 : DdCfg<N>::NT;
+  return MB && N >= 2048 ? 1024 : DdCfg<N, WIDE>::NT;
 }
 
-template <int N, bool SQ, bool MB>
-__global__ __launch_bounds__((dd_threads<N, MB>())) void k_dd_fft(float* __restrict__ Y,
+template <int N, bool SQ, bool MB, bool WIDE>
+__global__ __launch_bounds__((dd_threads<N, MB, WIDE>())) void k_dd_fft(float* __restrict__ Y,
                                                         const float* __restrict__ R,
                                                         const float2* __restrict__ tw, int L,
                                                         int BD, int fo, int lo, int d0, int dlen,
                                                         int ppl, int lm, int K, int r0) {
-  constexpr int CW = DdCfg<N>::CW, NT = dd_threads<N, MB>(), U = N / 2, HW = CW / 2;
+  constexpr int CW = DdCfg<N, WIDE>::CW, NT = dd_threads<N, MB, WIDE>(), U = N / 2, HW = CW / 2;
   __shared__ float2 buf[N * CW];
-  __shared__ float2 twl[DdCfg<N>::TWN];
-  const auto twz = dd_make_tw<N, NT>(twl, tw);
+  __shared__ float2 twl[DdCfg<N, WIDE>::TWN];
+  const auto twz = dd_make_tw<N, WIDE, NT>(twl, tw);
   const int q = fft::xcd_logical((int)blockIdx.x, (int)gridDim.x);
   const int units = ppl * lm;  // (layer, panel) units per output block
   const int rb = MB ? q / units : 0;
@@ -325,110 +382,142 @@ __global__ __launch_bounds__((dd_threads<N, MB>())) void k_dd_fft(float* __restr
   float* Ym = Y + (size_t)m * L * BD;
   const float* Rm = R + (size_t)m * L * BD;
 
-  constexpr int PUN = (U + 1) * CW;  // (bin kk <= U, column col) units
+  // Units (bin kk < U, column pair pr) of the spectra: the pair's two columns at
+  // bins kk and N - kk; unit kk = 0 takes the two real bins 0 and U instead,
+  // as one complex value each.  The pair's product spectra then meet in one
+  // thread, which writes the packed inverse input without a turn through LDS.
+  constexpr int PUN = U * HW;
   constexpr int PU = (PUN + NT - 1) / NT;
   constexpr float inv_n = 1.0f / (float)N;
-  // the forward transform of the packed block y + i rho at rows base ..
-  // base + U - 1 of the unit's columns, into buf
-  auto forward_block = [&](int base) {
-    fft::forward_from_global<N, CW, CW, NT, true>(buf, twz, [&](int row, int col) {
+  using FP = fft::FirstPass<N, CW, NT, true>;
+  // the packed block y + i rho at rows base .. base + U - 1 of the unit's columns
+  auto load_block = [&](int base, typename FP::In& in) {
+    fft::first_pass_load<N, CW, NT, true>(in, [&](int row, int col) {
       const int c = c0 + col;
       if (c >= BD) return make_float2(0.f, 0.f);
       const size_t e = (size_t)(base + row) * rs + c;
       return make_float2(Ym[e], Rm[e]);
     });
   };
+  auto forward_block = [&](const typename FP::In& in) {
+    fft::first_pass_regs<N, CW, CW, NT, false, true>(buf, in);
+    fft::lds_passes<N, 1, fft::Plan<N>::NP, CW, CW, NT, false>(buf, twz);
+  };
+  // spectra of y and rho of column h of the unit's pair
+  auto spectra = [&](int kk, int pr, int h, float2& ys, float2& rs2) {
+    const int ka = kk * CW + 2 * pr + h, kb = (kk ? N - kk : U) * CW + 2 * pr + h;
+    const float2 x = buf[ka], xm = buf[kb];
+    if (kk) {
+      unpack(x, xm, ys, rs2);
+    } else {
+      ys = make_float2(x.x, xm.x);
+      rs2 = make_float2(x.y, xm.y);
+    }
+  };
+  // p += a b / N (unit kk = 0: its two real bins each on their own)
+  auto add_product = [&](int kk, float2 a, float2 b, float2& p) {
+    const float2 v = kk ? cmul(a, b) : make_float2(a.x * b.x, a.y * b.y);
+    p.x = fmaf(v.x, inv_n, p.x);
+    p.y = fmaf(v.y, inv_n, p.y);
+  };
   const int r = MB ? r0 + 2 * rb : 0;
   const int pmin = MB ? (r - K + 1 > 0 ? r - K + 1 : 0) : 0;
   const int pmax = MB ? (r < K - 1 ? r : K - 1) : 0;
-  float2 p[PU];  // product spectrum of the unit's column, scaled by 1/N
+  float2 p[PU][2];  // product spectra of the unit's columns, scaled by 1/N
 #pragma unroll
-  for (int a = 0; a < PU; ++a) p[a] = make_float2(0.f, 0.f);
+  for (int a = 0; a < PU; ++a) p[a][0] = p[a][1] = make_float2(0.f, 0.f);
   for (int pb = pmin; pb <= pmax; ++pb) {
     const int qb = r - pb;
-    if (pb > pmin) __syncthreads();  // the previous pair's spectra have been read
-    // spectra of the fixed (sub-)block
-    forward_block(fo + pb * U);
-    float2 yf[PU], rf[PU];
+    const bool same = SQ && pb == qb;  // the square's block with itself
+    if (pb > pmin) __syncthreads();    // the previous pair's spectra have been read
+    // both blocks are loaded before the first transform (one round trip, the
+    // recent one's under that transform)
+    typename FP::In in, in2;
+    load_block(fo + pb * U, in);
+    load_block(same ? fo + pb * U : (SQ ? fo : lo) + qb * U, in2);
+    forward_block(in);
+    float2 yf[PU][2], rf[PU][2];
 #pragma unroll
     for (int a = 0; a < PU; ++a) {
       const int u = (int)threadIdx.x + a * NT;
-      yf[a] = rf[a] = make_float2(0.f, 0.f);
+      yf[a][0] = yf[a][1] = rf[a][0] = rf[a][1] = make_float2(0.f, 0.f);
       if (PUN % NT == 0 || u < PUN) {
-        const int kk = u / CW, col = u - kk * CW;
-        const int nk = (N - kk) & (N - 1);
-        unpack(buf[kk * CW + col], buf[nk * CW + col], yf[a], rf[a]);
+        const int kk = u / HW, pr = u - kk * HW;
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          spectra(kk, pr, h, yf[a][h], rf[a][h]);
+          if (same) add_product(kk, yf[a][h], rf[a][h], p[a][h]);
+        }
       }
     }
-    if (SQ && pb == qb) {
-#pragma unroll
-      for (int a = 0; a < PU; ++a) {
-        const float2 v = cmul(yf[a], rf[a]);
-        p[a].x = fmaf(v.x, inv_n, p[a].x);
-        p[a].y = fmaf(v.y, inv_n, p[a].y);
-      }
-    } else {
+    if (!same) {
       __syncthreads();  // every unit has read the fixed spectra
-      forward_block((SQ ? fo : lo) + qb * U);
+      forward_block(in2);
 #pragma unroll
       for (int a = 0; a < PU; ++a) {
         const int u = (int)threadIdx.x + a * NT;
         if (PUN % NT == 0 || u < PUN) {
-          const int kk = u / CW, col = u - kk * CW;
-          const int nk = (N - kk) & (N - 1);
-          float2 yr, rr;
-          unpack(buf[kk * CW + col], buf[nk * CW + col], yr, rr);
-          const float2 v = SQ ? cmul(yf[a], rr) : cadd(cmul(yf[a], rr), cmul(rf[a], yr));
-          p[a].x = fmaf(v.x, inv_n, p[a].x);
-          p[a].y = fmaf(v.y, inv_n, p[a].y);
+          const int kk = u / HW, pr = u - kk * HW;
+#pragma unroll
+          for (int h = 0; h < 2; ++h) {
+            float2 yr, rr;
+            spectra(kk, pr, h, yr, rr);
+            add_product(kk, yf[a][h], rr, p[a][h]);
+            if constexpr (!SQ) add_product(kk, rf[a][h], yr, p[a][h]);
+          }
         }
       }
     }
   }
-  // half spectra P[kk][col], kk <= U, into LDS; then the packed inverse
-  // input Q of every column pair over the whole buffer (after a barrier:
-  // the two layouts overlap)
+  // the packed inverse input Q = Pa + i Pb of every column pair over the whole
+  // buffer (Q[N - k] = conj Pa + i conj Pb)
   __syncthreads();
 #pragma unroll
   for (int a = 0; a < PU; ++a) {
     const int u = (int)threadIdx.x + a * NT;
-    if (PUN % NT == 0 || u < PUN) buf[u] = p[a];  // u = kk * CW + col
-  }
-  __syncthreads();
-  constexpr int QUN = (U + 1) * HW;
-  constexpr int QU = (QUN + NT - 1) / NT;
-  float2 qk[QU], qnk[QU];
-#pragma unroll
-  for (int a = 0; a < QU; ++a) {
-    const int u = (int)threadIdx.x + a * NT;
-    if (QUN % NT == 0 || u < QUN) {
+    if (PUN % NT == 0 || u < PUN) {
       const int kk = u / HW, pr = u - kk * HW;
-      const float2 pa = buf[kk * CW + 2 * pr], pb = buf[kk * CW + 2 * pr + 1];
-      qk[a] = make_float2(pa.x - pb.y, pa.y + pb.x);     // Pa + i Pb
-      qnk[a] = make_float2(pa.x + pb.y, pb.x - pa.y);    // conj Pa + i conj Pb
+      const float2 pa = p[a][0], pb = p[a][1];
+      const float2 lo2 = kk ? make_float2(pa.x - pb.y, pa.y + pb.x) : make_float2(pa.x, pb.x);
+      const float2 hi2 = kk ? make_float2(pa.x + pb.y, pb.x - pa.y) : make_float2(pa.y, pb.y);
+      buf[kk * HW + pr] = lo2;
+      buf[(kk ? N - kk : U) * HW + pr] = hi2;
     }
   }
-  __syncthreads();
-#pragma unroll
-  for (int a = 0; a < QU; ++a) {
-    const int u = (int)threadIdx.x + a * NT;
-    if (QUN % NT == 0 || u < QUN) {
-      const int kk = u / HW, pr = u - kk * HW;
-      const int nk = (N - kk) & (N - 1);
-      buf[kk * HW + pr] = qk[a];
-      if (nk != kk) buf[nk * HW + pr] = qnk[a];
-    }
-  }
-  __syncthreads();
   // rows of output block r inside the destination (its linear convolution
-  // has N - 1 rows; row N - 1 of the inverse is zero up to rounding)
+  // has N - 1 rows; row N - 1 of the inverse is zero up to rounding), loaded
+  // under the inverse transform
   const int rlen = dlen - r * U < N - 1 ? dlen - r * U : N - 1;
-  fft::inverse_to_global<N, HW, HW, NT, false>(buf, twz, [&](int row, int pr, float2 v) {
-    if (row >= rlen) return;
-    const int c = c0 + 2 * pr;
-    float* dst = Ym + (size_t)(d0 + r * U + row) * rs;
-    if (c < BD) dst[c] += v.x;
-    if (c + 1 < BD) dst[c + 1] += v.y;
+  using PL = fft::Plan<N>;
+  constexpr int RL = PL::radix(PL::NP - 1);
+  constexpr int LU = (N / RL * HW + NT - 1) / NT;
+  float* dst = Ym + (size_t)(d0 + r * U) * rs;
+  float2 zo[LU][RL];
+  auto last = [&](auto f) {
+#pragma unroll
+    for (int a = 0; a < LU; ++a) {
+      const int u = (int)threadIdx.x + a * NT;
+      if ((N / RL * HW) % NT == 0 || u < N / RL * HW) {
+        const int j = u / HW, c = c0 + 2 * (u - j * HW);
+#pragma unroll
+        for (int s = 0; s < RL; ++s) {
+          const int row = j + s * (N / RL);
+          if (row < rlen && c < BD) f(a, s, dst + (size_t)row * rs + c, c + 1 < BD);
+        }
+      }
+    }
+  };
+  last([&](int a, int s, float* q, bool two) { zo[a][s] = make_float2(q[0], two ? q[1] : 0.f); });
+  __syncthreads();
+  fft::lds_passes<N, 0, PL::NP - 1, HW, HW, NT, true>(buf, twz);
+  int la = 0, ls = 0;
+  fft::last_pass_global<N, HW, HW, NT, true, false>(buf, twz, [&](int, int, float2 v) {
+    zo[la][ls] = make_float2(zo[la][ls].x + v.x, zo[la][ls].y + v.y);
+    if (++ls == RL) ls = 0, ++la;
+  });
+  last([&](int a, int s, float* q, bool two) {
+    q[0] = zo[a][s].x;
+    if (two) q[1] = zo[a][s].y;
   });
 }
 
@@ -538,21 +627,28 @@ hipError_t dd_fft(lcsm_dd* c, int U, int lo, int d0, int dlen) {
   const int V = N / 2, K = U / V;
   // output blocks that start inside the destination (r V < dlen), at most 2K - 1
   const int nb = (dlen + V - 1) / V < 2 * K - 1 ? (dlen + V - 1) / V : 2 * K - 1;
+  const bool wide = (long long)c->M * c->BD >= lcsm::kDdWideMinCols;
+#define LCSM_DD_ONE(NN, WIDE)                                                                     \
+  {                                                                                               \
+    const int ppl = (c->BD + lcsm::dd_cw<NN>(WIDE) - 1) / lcsm::dd_cw<NN>(WIDE);                  \
+    hipLaunchKernelGGL((lcsm::k_dd_fft<NN, SQ, false, WIDE>), dim3((unsigned)(ppl * c->M)),       \
+                       dim3(lcsm::dd_threads<NN, false, WIDE>()), 0, c->stream, c->Y, c->R,       \
+                       c->tw, c->L, c->BD, U, lo, d0, dlen, ppl, c->M, 1, 0);                     \
+    return hipGetLastError();                                                                     \
+  }
 #define LCSM_CASE(NN)                                                                             \
   case NN: {                                                                                      \
-    constexpr int CW = lcsm::DdCfg<NN>::CW;                                                       \
-    const int ppl = (c->BD + CW - 1) / CW;                                                        \
     if (K == 1) {                                                                                 \
-      hipLaunchKernelGGL((lcsm::k_dd_fft<NN, SQ, false>), dim3((unsigned)(ppl * c->M)),           \
-                         dim3(lcsm::DdCfg<NN>::NT), 0, c->stream, c->Y, c->R, c->tw, c->L, c->BD, \
-                         U, lo, d0, dlen, ppl, c->M, 1, 0);                                       \
-      return hipGetLastError();                                                                   \
+      if constexpr (lcsm::dd_cw<NN>(true) != lcsm::dd_cw<NN>(false))                              \
+        if (wide) LCSM_DD_ONE(NN, true)                                                           \
+      LCSM_DD_ONE(NN, false)                                                                      \
     }                                                                                             \
+    const int ppl = (c->BD + lcsm::dd_cw<NN>(false) - 1) / lcsm::dd_cw<NN>(false);                \
     for (int r0 = 0; r0 < 2 && r0 < nb; ++r0) {                                                   \
       const int nr = (nb - r0 + 1) / 2;                                                           \
-      hipLaunchKernelGGL((lcsm::k_dd_fft<NN, SQ, true>), dim3((unsigned)(nr * ppl * c->M)),       \
-                         dim3(lcsm::dd_threads<NN, true>()), 0, c->stream, c->Y, c->R, c->tw, c->L, c->BD, \
-                         U, lo, d0, dlen, ppl, c->M, K, r0);                                      \
+      hipLaunchKernelGGL((lcsm::k_dd_fft<NN, SQ, true, false>), dim3((unsigned)(nr * ppl * c->M)), \
+                         dim3(lcsm::dd_threads<NN, true, false>()), 0, c->stream, c->Y, c->R,     \
+                         c->tw, c->L, c->BD, U, lo, d0, dlen, ppl, c->M, K, r0);                  \
       const hipError_t e = hipGetLastError();                                                     \
       if (e != hipSuccess) return e;                                                              \
     }                                                                                             \
@@ -573,6 +669,7 @@ hipError_t dd_fft(lcsm_dd* c, int U, int lo, int d0, int dlen) {
     LCSM_CASE(8192)
   }
 #undef LCSM_CASE
+#undef LCSM_DD_ONE
   return hipErrorInvalidValue;
 }
 
@@ -583,15 +680,11 @@ hipError_t dd_tile(lcsm_dd* c, bool square, int U, int lo, int d0, int dlen) {
     return square ? dd_fft<true>(c, U, lo, d0, dlen) : dd_fft<false>(c, U, lo, d0, dlen);
   const dim3 grid((unsigned)((c->BD + lcsm::kThreads - 1) / lcsm::kThreads),
                   (unsigned)((dlen + lcsm::kDdJ - 1) / lcsm::kDdJ), (unsigned)c->M);
-#define LCSM_DD_U(UU)                                                                              \
-  if (U == UU) {                                                                                   \
-    if (square)                                                                                    \
-      hipLaunchKernelGGL((lcsm::k_dd_direct_u<lcsm::kDdJ, UU, true>), grid, dim3(lcsm::kThreads), 0, \
-                         c->stream, c->Y, c->R, c->L, c->BD, lo, d0, dlen);                        \
-    else                                                                                           \
-      hipLaunchKernelGGL((lcsm::k_dd_direct_u<lcsm::kDdJ, UU, false>), grid, dim3(lcsm::kThreads),   \
-                         0, c->stream, c->Y, c->R, c->L, c->BD, lo, d0, dlen);                     \
-    return hipGetLastError();                                                                      \
+#define LCSM_DD_U(UU)                                                                            \
+  if (square && U == UU) {                                                                       \
+    hipLaunchKernelGGL((lcsm::k_dd_square_u<lcsm::kDdJ, UU>), grid, dim3(lcsm::kThreads), 0,     \
+                       c->stream, c->Y, c->R, c->L, c->BD, lo, d0, dlen);                        \
+    return hipGetLastError();                                                                    \
   }
   LCSM_DD_U(16)
   LCSM_DD_U(32)
@@ -692,17 +785,27 @@ int lcsm_dd_step(lcsm_dd* c, const float* y_t, const float* rho_t, float* z_t) {
                                                             : lcsm::kDdFusedMaxU;
   int uf = 0;
   for (int U = 1; U <= fmax && i1 % U == 0 && 2 * U <= i1; U *= 2) uf = U;
+  if (uf == lcsm::kDdFusedMaxU)
+    for (int U = 2 * uf; U <= lcsm::kDdWideMaxU && U <= c->opt.direct_max_u && i1 % U == 0 && 2 * U < i1;
+         U *= 2)
+      uf = U;
   const dim3 rgrid((unsigned)((c->BD + lcsm::kThreads - 1) / lcsm::kThreads), (unsigned)c->M);
 #define LCSM_DD_STEP(UU)                                                                        \
   hipLaunchKernelGGL((lcsm::k_dd_step<UU>), rgrid, dim3(lcsm::kThreads), 0, c->stream, y_t,    \
+                     rho_t, z_t, c->Y, c->R, c->L, c->BD, t)
+#define LCSM_DD_WIDE(UU)                                                                        \
+  hipLaunchKernelGGL((lcsm::k_dd_step_wide<UU>), rgrid, dim3(lcsm::kThreads), 0, c->stream, y_t, \
                      rho_t, z_t, c->Y, c->R, c->L, c->BD, t)
   switch (uf) {
     case 0: LCSM_DD_STEP(0); break;
     case 1: LCSM_DD_STEP(1); break;
     case 2: LCSM_DD_STEP(2); break;
     case 4: LCSM_DD_STEP(4); break;
-    default: LCSM_DD_STEP(8); break;
+    case 8: LCSM_DD_STEP(8); break;
+    case 16: LCSM_DD_WIDE(16); break;
+    default: LCSM_DD_WIDE(32); break;
   }
+#undef LCSM_DD_WIDE
 #undef LCSM_DD_STEP
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return dd_fail(c, LCSM_EDEVICE, "red-cell launch", e);

@@ -357,35 +357,52 @@ __device__ __forceinline__ void lds_passes(float2* buf, const TW& tw) {
   }
 }
 
-// First pass (index 0, p = 1, no twiddles) with inputs fetched by
-// load(row, col) instead of from LDS; only rows < N*QIN/R are fetched (the
-// rest are zero: QIN = R/2 for a zero-padded upper half, R for full input).
-// Writes its outputs to LDS and synchronises.
-template <int N, int WC, int LDSW, int NT, bool INV, bool HALF, int SH = 0, class Load>
-__device__ __forceinline__ void first_pass_global(float2* buf, const Load& load) {
-  constexpr int R = Plan<N>::radix(0);
-  constexpr int QIN = HALF ? R / 2 : R;
-  constexpr int UNITS = N / R * WC;
-  constexpr int UPT = (UNITS + NT - 1) / NT;
-  float2 v[UPT][R];
+// Butterflies of the first pass per thread, and inputs of each (the rest are
+// zero: half of them for a zero-padded upper half).
+template <int N, int WC, int NT, bool HALF>
+struct FirstPass {
+  static constexpr int R = Plan<N>::radix(0);
+  static constexpr int QIN = HALF ? R / 2 : R;
+  static constexpr int UNITS = N / R * WC;
+  static constexpr int UPT = (UNITS + NT - 1) / NT;
+  using In = float2[UPT][QIN];
+};
+
+// The inputs of the thread's first-pass butterflies, fetched by load(row, col).
+template <int N, int WC, int NT, bool HALF, class Load>
+__device__ __forceinline__ void first_pass_load(
+    typename FirstPass<N, WC, NT, HALF>::In& in, const Load& load) {
+  using F = FirstPass<N, WC, NT, HALF>;
 #pragma unroll
-  for (int a = 0; a < UPT; ++a) {
+  for (int a = 0; a < F::UPT; ++a) {
     const int u = (int)threadIdx.x + a * NT;
-    if (UNITS % NT == 0 || u < UNITS) {
+    if (F::UNITS % NT == 0 || u < F::UNITS) {
       const int j = u / WC, col = u % WC;
 #pragma unroll
-      for (int q = 0; q < R; ++q) v[a][q] = (q < QIN) ? load(j + q * (N / R), col) : make_float2(0.f, 0.f);
+      for (int q = 0; q < F::QIN; ++q) in[a][q] = load(j + q * (N / F::R), col);
     }
   }
+}
+
+// First pass (index 0, p = 1, no twiddles) from registers into LDS;
+// synchronises at the end.
+template <int N, int WC, int LDSW, int NT, bool INV, bool HALF, int SH = 0>
+__device__ __forceinline__ void first_pass_regs(
+    float2* buf, const typename FirstPass<N, WC, NT, HALF>::In& in) {
+  using F = FirstPass<N, WC, NT, HALF>;
+  constexpr int R = F::R;
 #pragma unroll
-  for (int a = 0; a < UPT; ++a) {
+  for (int a = 0; a < F::UPT; ++a) {
     const int u = (int)threadIdx.x + a * NT;
-    if (UNITS % NT == 0 || u < UNITS) {
+    if (F::UNITS % NT == 0 || u < F::UNITS) {
       const int j = u / WC, col = u % WC;
-      dft<R, INV>(v[a]);
+      float2 v[R];
+#pragma unroll
+      for (int q = 0; q < R; ++q) v[q] = (q < F::QIN) ? in[a][q < F::QIN ? q : 0] : make_float2(0.f, 0.f);
+      dft<R, INV>(v);
       if constexpr (SH == 0) {
 #pragma unroll
-        for (int s = 0; s < R; ++s) buf[(j * R + s) * LDSW + col] = v[a][s];
+        for (int s = 0; s < R; ++s) buf[(j * R + s) * LDSW + col] = v[s];
       } else {
         // one column only: j R is a multiple of R, so for s < R the slot of
         // j R + s is that of j R plus s plus the padding within s
@@ -394,14 +411,24 @@ __device__ __forceinline__ void first_pass_global(float2* buf, const Load& load)
 #pragma unroll
         for (int s = 0; s < R; ++s) {
           if constexpr (R <= (1 << SH))
-            buf[b + s] = v[a][s];
+            buf[b + s] = v[s];
           else
-            buf[b + s + (s >> SH)] = v[a][s];
+            buf[b + s + (s >> SH)] = v[s];
         }
       }
     }
   }
   __syncthreads();
+}
+
+// First pass with inputs fetched by load(row, col) instead of from LDS; only
+// rows < N*QIN/R are fetched.  Writes its outputs to LDS and synchronises.
+template <int N, int WC, int LDSW, int NT, bool INV, bool HALF, int SH = 0, class Load>
+__device__ __forceinline__ void first_pass_global(float2* buf, const Load& load) {
+  using F = FirstPass<N, WC, NT, HALF>;
+  typename F::In in;
+  first_pass_load<N, WC, NT, HALF>(in, load);
+  first_pass_regs<N, WC, LDSW, NT, INV, HALF, SH>(buf, in);
 }
 
 // Last pass (index NP-1, p = N/R) reading LDS and handing the outputs of

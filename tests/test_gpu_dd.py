@@ -161,3 +161,55 @@ def test_dd_workload_sizes_sampled_columns(name):
     err = rel_err(zg, zr)
     say(f"  sampled rel err {err:.3e}")
     assert err <= TOL
+
+
+@pytest.mark.parametrize("L", [31, 48, 49, 64, 65, 80, 96, 97, 127, 161])
+@pytest.mark.parametrize("dmax", [0, 8, 16, 64])
+def test_dd_wide_steps(L, dmax):
+    """The tiles of 16 and 32 inside the step (rectangles; the squares of t + 1 =
+    32 and 64 on their own), destinations whole and clipped at L, direct limits
+    that leave one or both out: exact on small integers (sums below 2^24)."""
+    M, B, D = 2, 1, 67
+    w = datagen.Workload("dd_wide", M, B, D, L, decay=20.0, seed=L + dmax)
+    say(f"[dd wide steps] L={L} direct_max_u={dmax}")
+    y, rho = datagen.int_y_np(w), datagen.int_rho_np(w)
+    yd, rd = (torch.from_numpy(a.astype(np.float32)).to(dev()) for a in (y, rho))
+    ctx = lcsm_mod().Dd(M, B, D, L, options={"direct_max_u": dmax} if dmax else None)
+    z = torch.full_like(yd, float("nan"))
+    for t in range(L):
+        ctx.step(yd[t], rd[t], z[t])
+    torch.cuda.synchronize()
+    ctx.close()
+    ref = np.zeros((2 * L - 1, M * B * D), dtype=np.int64)
+    yi, ri = y.reshape(L, -1).astype(np.int64), rho.reshape(L, -1).astype(np.int64)
+    for j in range(L):
+        ref[j:j + L] += yi[j] * ri
+    zg = z.cpu().numpy().reshape(L, -1)
+    if 4 * (dmax or 32) < L:  # the square of twice the direct limit is reached, an FFT tile: round
+        assert np.abs(zg - ref[:L]).max() < 0.25
+        zg = np.rint(zg)
+    assert np.array_equal(zg.astype(np.int64), ref[:L])
+
+
+@pytest.mark.parametrize("BD", [1 << 17, (1 << 17) + 5, (1 << 17) + 31])
+def test_dd_wide_panels(BD):
+    """Panels of 32 columns of 2U = 64 to 256 (from 2^17 columns), the last one
+    whole and ragged, odd column counts: sampled columns against numpy in fp64."""
+    L = 600
+    say(f"[dd wide panels] BD={BD}")
+    g = torch.Generator(device=dev())
+    g.manual_seed(BD)
+    y = torch.rand((L, 1, 1, BD), device=dev(), generator=g) - 0.5
+    rho = torch.rand((L, 1, 1, BD), device=dev(), generator=g) - 0.5
+    ctx = lcsm_mod().Dd(1, 1, BD, L, options={"direct_max_u": 16})
+    z = torch.full_like(y, float("nan"))
+    for t in range(L):
+        ctx.step(y[t], rho[t], z[t])
+    torch.cuda.synchronize()
+    ctx.close()
+    assert torch.isfinite(z).all()
+    cols = sorted({0, 1, 15, 16, 31, 32, 33, BD // 2, BD - 37, BD - 32, BD - 6, BD - 5, BD - 2, BD - 1})
+    ys, rs, zs = (a.view(L, BD)[:, cols].double().cpu().numpy() for a in (y, rho, z))
+    zr = np.stack([np.convolve(ys[:, k], rs[:, k])[:L] for k in range(len(cols))], axis=1)
+    # sums of at most 10 tiles a row, each within about 10 roundings of its transforms
+    assert rel_err(zs, zr) <= 10 * 10 * 2.0 ** -24
