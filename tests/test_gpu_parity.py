@@ -281,3 +281,34 @@ def test_integer_data_at_the_layer_and_batch_limits(opt, shape):
     else:
         assert np.abs(z.astype(np.float64) - ex).max() < 0.25
         assert np.array_equal(np.rint(z).astype(np.int64), ex)
+
+
+@pytest.mark.parametrize("D", [1, 63, 255, 256, 257, 513])
+@pytest.mark.parametrize("L", [2, 3, 37, 64, 97])
+def test_step_edges_integer_exact(D, L):
+    """Step launches at the edges of their channel blocks (the lanes past D in
+    the last one load column D - 1) and of the sequence (the last tile of every
+    size whole, clipped, absent), steps and advance after per-layer red cells:
+    bit for bit the int64 convolution (sums below 2^24)."""
+    M, B = 2, 3
+    w = datagen.Workload("step_edges", M, B, D, L, decay=8.0, seed=D + L)
+    h, y = datagen.int_filters_np(w), datagen.int_y_np(w)
+    hd, yd = (torch.from_numpy(a.astype(np.float32)).to(dev()) for a in (h, y))
+    ctx = lcsm_mod().Lcsm(hd, B, options={"direct_max_u": 64})
+    z = torch.full_like(yd, float("nan"))
+    z2 = torch.full_like(yd, float("nan"))
+    for t in range(L):
+        ctx.step(yd[t], z[t])
+    ctx.reset()
+    for t in range(L):
+        for m in range(M):
+            ctx.step_layer(m, yd[t, m], z2[t, m])
+        ctx.advance()
+    torch.cuda.synchronize()
+    ctx.close()
+    hc = np.broadcast_to(h.astype(np.int64).transpose(2, 0, 1)[:, :, None, :], (L, M, B, D))
+    ref = np.zeros((2 * L, M, B, D), dtype=np.int64)
+    for s in range(L):
+        ref[s:s + L] += y[s].astype(np.int64) * hc
+    assert np.array_equal(z.cpu().numpy().astype(np.int64), ref[:L])
+    assert torch.equal(z, z2)
