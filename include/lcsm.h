@@ -294,7 +294,9 @@ void lcsm_graph_destroy(lcsm_graph* g);
  * (above the direct crossover) the work is: copy the prompt into the state,
  * one 2P-point tile with the filter spectrum delayed by P rows (its outputs
  * are the causal convolution of the prompt), the same tile with the cached
- * spectrum; the spectra of tile size P are recomputed twice in place.  For a
+ * spectrum.  For a mirrored tile size both run on the mirror, the delayed
+ * spectra made in the scratch; otherwise (or where one layer's do not fit
+ * there) the spectra of tile size P are recomputed twice in place.  For a
  * direct tile size it runs the P ordinary steps.  Errors: LCSM_EINVAL (null
  * pointers, P not a power of two, 2P > L, or 2P > T with half_state),
  * LCSM_ESTATE (not at position 0, or faulted), LCSM_EDEVICE. */
