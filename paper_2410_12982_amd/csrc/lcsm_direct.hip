@@ -63,7 +63,7 @@ __global__ __launch_bounds__(kThreads) void k_step_fused(const float* __restrict
                                                         float* __restrict__ St,
                                                         const float* __restrict__ Hf, size_t ls,
                                                         size_t hls, int BD, int D, int rows,
-                                                        int lags, int dst_len) {
+                                                        int lags) {
   constexpr int SP = U > 0 ? Split<U>::value : 1;
   constexpr int UJ = U > 0 ? U / SP : 1;  // outputs per thread
   const unsigned c0 = blockIdx.x * kThreads, left = (unsigned)D - c0;
@@ -90,7 +90,8 @@ __global__ __launch_bounds__(kThreads) void k_step_fused(const float* __restrict
   // Every load is unconditional, with its row or lag clamped into range
   // (values past the end are never used): loads under a condition are issued
   // only after the earlier ones have returned, a second round trip per step.
-  // rows, lags: how many rows after t and lags there are.
+  // rows, lags: how many rows after t and lags there are (the tile's outputs
+  // are the first min(U, rows)); the arguments fill one line of 64 bytes.
   float yt, acc = 0.f, h0 = 0.f;
   if constexpr (RED) {
     yt = at(y + slab);
@@ -146,7 +147,7 @@ __global__ __launch_bounds__(kThreads) void k_step_fused(const float* __restrict
     yb[U - 1] = yt;
 #pragma unroll
     for (int jj = 0; jj < UJ; ++jj) {
-      if (FULL || j0 + jj < dst_len) {
+      if (FULL || j0 + jj < rows) {
         float o = 0.f;
 #pragma unroll
         for (int k = 0; k < U; ++k) o = fmaf(yb[k], hh[U + jj - k], o);
@@ -703,7 +704,7 @@ hipError_t dispatch_fused(int U, const float* y, float* z, float* S, const float
   hipLaunchKernelGGL((k_step_fused<UU, RED, FULL>),                                              \
                      dim3(blocks_for(s.D), (unsigned)s.B, (unsigned)(mc * SP)), block, 0, st,    \
                      y + (RED ? (size_t)m0 * s.BD : 0), z + (RED ? (size_t)m0 * s.BD : 0),       \
-                     St + m0 * ls, Hf + m0 * hls, ls, hls, s.BD, s.D, s.L - 1 - t, s.L, dst_len)
+                     St + m0 * ls, Hf + m0 * hls, ls, hls, s.BD, s.D, s.L - 1 - t, s.L)
 #define LCSM_FUSED_CASE(UU)                                                                      \
   case UU: {                                                                                     \
     constexpr int SP = UU > 0 ? Split<UU>::value : 1;                                            \
