@@ -198,7 +198,9 @@ __global__ __launch_bounds__(kThreads) void k_chain_fused(const float* __restric
   const int c = (int)blockIdx.y * D + d;
   const size_t rs = (size_t)BD;
   const bool tile = (U > 0) && (dst_len > 0);
-  float sl = 0.f;  // s of z^{M-1}_{t-1} (loaded with the first chunk), then of z^{m-1}_t
+  // s of z^{M-1}_{t-1} (first in the chain, so loaded ahead of the chunks;
+  // unused at t = 0), then of z^{m-1}_t
+  float sl = prev[c];
   for (int m0 = 0; m0 < M; m0 += K) {
     float xv[K], acc[K], h0[K];
     float yb[K][NY], hh[K][NH], zo[K][NZ];
@@ -227,7 +229,22 @@ __global__ __launch_bounds__(kThreads) void k_chain_fused(const float* __restric
         }
       }
     }
-    if (m0 == 0) sl = prev[c];  // unused at t = 0
+    // Pinned after the last load, as in k_step_fused: carrying s, the compiler
+    // sank the first tile's row into its condition behind the chain, a round
+    // trip more per step (512 positions of 32 x 16 x 2048: 11.15 -> 10.98 ms,
+    // 12 x 16 x 1024 4.02 -> 3.93; carrying z, without the pin, 10.96 and 3.89).
+#pragma unroll
+    for (int kk = 0; kk < K; ++kk) {
+      asm volatile("" : "+v"(xv[kk]), "+v"(acc[kk]), "+v"(h0[kk]));
+      if constexpr (U > 0) {
+#pragma unroll
+        for (int k = 0; k < U - 1; ++k) asm volatile("" : "+v"(yb[kk][k]));
+#pragma unroll
+        for (int l = 1; l < 2 * U; ++l) asm volatile("" : "+v"(hh[kk][l]));
+#pragma unroll
+        for (int j = 0; j < U; ++j) asm volatile("" : "+v"(zo[kk][j]));
+      }
+    }
     // the chain through the chunk, then its stores
 #pragma unroll
     for (int kk = 0; kk < K; ++kk) {
