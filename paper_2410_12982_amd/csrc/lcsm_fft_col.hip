@@ -847,15 +847,16 @@ __global__ __launch_bounds__(ColCfg<NS>::NT, ColCfg<NS>::MINB) void k_cm_tile2(
 // Spectra of the filters' first P taps, delayed by P, for the prompt's own
 // outputs: Hc[g][k] = (-1)^k DFT_2P(h_g[0, P))[k] / 2P for the columns g = m D
 // + d of X[g][r] = h[m, d, r] (r < P, contiguous; the delay by half the length
-// is the sign).  One pair of columns per workgroup, the second absent at an
-// odd end: z = h_a + i h_b, Ha = (Z[k] + conj Z[2P-k]) / 2, Hb = (Z[k] -
+// is the sign).  One pair of channels of a layer per workgroup, the last one
+// alone when D is odd (a pair shares rounding and non-finite values, so none
+// reaches over layers, whose scales may differ, and the pairs do not depend on
+// the chunk): z = h_a + i h_b, Ha = (Z[k] + conj Z[2P-k]) / 2, Hb = (Z[k] -
 // conj Z[2P-k]) / 2i.  Contiguous reads and writes; the general path (four-step
 // over the lag-major taps) took 1.9 ms for 13824 filters at 2P = 16384, this
 // one with its transpose 0.57 ms.
 template <int N>
 __global__ __launch_bounds__(ColCfg<N>::NT, ColCfg<N>::MINB) void k_prompt_spectra(
-    const float* __restrict__ X, float2* __restrict__ Hc, const float2* __restrict__ tw,
-    int ncols) {
+    const float* __restrict__ X, float2* __restrict__ Hc, const float2* __restrict__ tw, int D) {
   constexpr int NT = ColCfg<N>::NT, U = N / 2, SH = ColCfg<N>::SH;
   using TW = typename std::conditional<ColCfg<N>::TWL, fft::TwLds<N>, TwSplit<N>>::type;
   __shared__ float2 buf[ColCfg<N>::SLOTS];
@@ -869,8 +870,10 @@ __global__ __launch_bounds__(ColCfg<N>::NT, ColCfg<N>::MINB) void k_prompt_spect
     for (int l = (int)threadIdx.x; l < 64; l += NT) twl[N / 64 + l] = tw[N + l];
     twz = TW{twl, twl + N / 64};
   }
-  const int g = 2 * (int)blockIdx.x;
-  const bool hasb = g + 1 < ncols;
+  const int ppl = (D + 1) / 2;  // pairs per layer
+  const int m = (int)blockIdx.x / ppl, d = 2 * ((int)blockIdx.x - m * ppl);
+  const int g = m * D + d;
+  const bool hasb = d + 1 < D;
   const float* xa = X + (size_t)g * U;
   fft::forward_from_global<N, 1, 1, NT, true, SH>(buf, twz, [&](int row, int) {
     return make_float2(xa[row], hasb ? xa[U + row] : 0.f);
@@ -889,8 +892,7 @@ __global__ __launch_bounds__(ColCfg<N>::NT, ColCfg<N>::MINB) void k_prompt_spect
 // (NS - kk - PAR) mod NS of the same half.
 template <int NS, int PAR>
 __global__ __launch_bounds__(ColCfg<NS>::NT, ColCfg<NS>::MINB) void k_prompt_spectra2(
-    const float* __restrict__ X, float2* __restrict__ Hc, const float2* __restrict__ tw,
-    int ncols) {
+    const float* __restrict__ X, float2* __restrict__ Hc, const float2* __restrict__ tw, int D) {
   constexpr int NT = ColCfg<NS>::NT, U = NS, N = 2 * NS, SH = ColCfg<NS>::SH;
   __shared__ float2 buf[ColCfg<NS>::SLOTS];
   __shared__ float2 twl[NS / 64 + 64];
@@ -898,8 +900,10 @@ __global__ __launch_bounds__(ColCfg<NS>::NT, ColCfg<NS>::MINB) void k_prompt_spe
   for (int l = (int)threadIdx.x; l < 64; l += NT) twl[NS / 64 + l] = tw[NS + l];
   const TwSplit<NS> twz{twl, twl + NS / 64};
   constexpr int CC = NS / 16;
-  const int g = 2 * (int)blockIdx.x;
-  const bool hasb = g + 1 < ncols;
+  const int ppl = (D + 1) / 2;  // pairs per layer
+  const int m = (int)blockIdx.x / ppl, d = 2 * ((int)blockIdx.x - m * ppl);
+  const int g = m * D + d;
+  const bool hasb = d + 1 < D;
   const float* xa = X + (size_t)g * U;
   fft::forward_from_global<NS, 1, 1, NT, false, SH>(buf, twz, [&](int row, int) -> float2 {
     const float2 v = make_float2(xa[row], hasb ? xa[U + row] : 0.f);
@@ -1104,11 +1108,11 @@ hipError_t launch_prompt_spectra(const float* Hf, float2* Hc, const float2* tw, 
   else
     hipLaunchKernelGGL(k_rows_to_cols, tin, dim3(kTThreads), 0, st, Hf, lstride, s.D, 0, P,
                        (long long)m0 * s.D, nc, X, P);
-  const dim3 grid((unsigned)((nc + 1) / 2));
+  const dim3 grid((unsigned)(nm * ((s.D + 1) / 2)));
   switch (N) {
 #define LCSM_PS_CASE(NN)                                                                         \
   case NN:                                                                                       \
-    hipLaunchKernelGGL(k_prompt_spectra<NN>, grid, dim3(ColCfg<NN>::NT), 0, st, X, Hc, tw, nc);  \
+    hipLaunchKernelGGL(k_prompt_spectra<NN>, grid, dim3(ColCfg<NN>::NT), 0, st, X, Hc, tw, s.D); \
     break;
     LCSM_PS_CASE(4) LCSM_PS_CASE(8) LCSM_PS_CASE(16) LCSM_PS_CASE(32) LCSM_PS_CASE(64)
     LCSM_PS_CASE(128) LCSM_PS_CASE(256) LCSM_PS_CASE(512) LCSM_PS_CASE(1024)
@@ -1116,9 +1120,9 @@ hipError_t launch_prompt_spectra(const float* Hf, float2* Hc, const float2* tw, 
 #undef LCSM_PS_CASE
     case 2 * kMaxColFftN1:
       hipLaunchKernelGGL((k_prompt_spectra2<kMaxColFftN1, 0>), grid, dim3(ColCfg<kMaxColFftN1>::NT),
-                         0, st, X, Hc, tw, nc);
+                         0, st, X, Hc, tw, s.D);
       hipLaunchKernelGGL((k_prompt_spectra2<kMaxColFftN1, 1>), grid, dim3(ColCfg<kMaxColFftN1>::NT),
-                         0, st, X, Hc, tw, nc);
+                         0, st, X, Hc, tw, s.D);
       break;
     default:
       return hipErrorInvalidValue;

@@ -179,3 +179,46 @@ def test_prefill_on_the_mirror(case):
     # sums over at most 16 levels of tiles, each within about 10 roundings of its 2U-point transforms
     assert err <= 16 * 10 * 2.0 ** -24
     ctx.close()
+
+
+@pytest.mark.parametrize("case", [
+    # (M, B, D, L, P, scratch_mib of the second context)
+    (3, 2, 5, 512, 64, 0),
+    (2, 3, 37, 500, 32, 0),
+    (4, 2, 1, 300, 128, 0),           # one channel a layer
+    (5, 1, 33, 4100, 2048, 2),        # two layers' spectra at a time
+    (2, 2, 3, 32768, 16384, 0),       # the transform as two halves
+])
+def test_mirrored_prompt_keeps_layers_apart(case):
+    """Odd D: the last channel of a layer shares its delayed spectrum's
+    transform with no channel of the next layer.  Whatever layer 0's taps are
+    (10^4 times as large, one of them not finite), the other layers' prompt
+    outputs and the steps behind them keep their bits, and so does everything
+    where the layers are taken in other chunks."""
+    M, B, D, L, P, mib = case
+    say(f"[prefill layers apart] {case}")
+    w = datagen.Workload("prefill_la", M, B, D, L, decay=max(L / 8, 8.0), seed=11 + P)
+    n = P + 70
+    y = datagen.y_torch(w, dev())[:n].contiguous()
+    h = datagen.filters_torch(w, dev())
+
+    def run(filters, **opts):
+        ctx, _ = make_ctx(w, filters, {"direct_max_u": 1, "col_fft_min_n": 4, **opts})
+        z = torch.full_like(y, float("nan"))
+        ctx.prefill(y[:P], z[:P])
+        ctx.run(y[P:], z[P:])
+        torch.cuda.synchronize()
+        ctx.close()
+        return z
+
+    z = run(h)
+    assert torch.isfinite(z).all()
+    large, bad = h.clone(), h.clone()
+    large[0] *= 1e4
+    bad[0, D - 1, 3] = float("nan")
+    assert torch.equal(run(large)[:, 1:], z[:, 1:])
+    zb = run(bad)
+    assert torch.equal(zb[:, 1:], z[:, 1:])
+    assert torch.isnan(zb[3:P, 0, :, D - 1]).all()
+    if mib:
+        assert torch.equal(run(h, scratch_mib=mib), z)
