@@ -851,25 +851,21 @@ __global__ __launch_bounds__(ColCfg<NS>::NT, ColCfg<NS>::MINB) void k_cm_tile2(
 // alone when D is odd (a pair shares rounding and non-finite values, so none
 // reaches over layers, whose scales may differ, and the pairs do not depend on
 // the chunk): z = h_a + i h_b, Ha = (Z[k] + conj Z[2P-k]) / 2, Hb = (Z[k] -
-// conj Z[2P-k]) / 2i.  Contiguous reads and writes; the general path (four-step
-// over the lag-major taps) took 1.9 ms for 13824 filters at 2P = 16384, this
-// one with its transpose 0.57 ms.
+// conj Z[2P-k]) / 2i.  Twiddles come from the table as it is: made of products as
+// in the tiles (TwSplit), for 0.06 ms less, the prompt's outputs were off by
+// 2.44e-7 instead of 2.30e-7 at P = 8192 and by 3.38e-7 instead of 2.81e-7 at
+// 1024 (the general path: 2.31e-7 and 2.81e-7).  Contiguous reads and writes; the
+// general path (four-step over the lag-major taps) took 1.9 ms for 13824 filters
+// at 2P = 16384, this one with its transpose 0.63 ms.
 template <int N>
 __global__ __launch_bounds__(ColCfg<N>::NT, ColCfg<N>::MINB) void k_prompt_spectra(
     const float* __restrict__ X, float2* __restrict__ Hc, const float2* __restrict__ tw, int D) {
   constexpr int NT = ColCfg<N>::NT, U = N / 2, SH = ColCfg<N>::SH;
-  using TW = typename std::conditional<ColCfg<N>::TWL, fft::TwLds<N>, TwSplit<N>>::type;
+  using TW = typename std::conditional<ColCfg<N>::TWL, fft::TwLds<N>, fft::TwGlobal>::type;
   __shared__ float2 buf[ColCfg<N>::SLOTS];
-  __shared__ float2 twl[ColCfg<N>::TWL ? N : N / 64 + 64];
-  TW twz;
-  if constexpr (ColCfg<N>::TWL) {
-    fft::load_twiddles<N, NT>(twl, tw);
-    twz = TW{twl};
-  } else {
-    for (int j = (int)threadIdx.x; j < N / 64; j += NT) twl[j] = tw[N + 64 * j];
-    for (int l = (int)threadIdx.x; l < 64; l += NT) twl[N / 64 + l] = tw[N + l];
-    twz = TW{twl, twl + N / 64};
-  }
+  __shared__ float2 twl[ColCfg<N>::TWL ? N : 1];
+  if constexpr (ColCfg<N>::TWL) fft::load_twiddles<N, NT>(twl, tw);
+  const TW twz{ColCfg<N>::TWL ? twl : tw};
   const int ppl = (D + 1) / 2;  // pairs per layer
   const int m = (int)blockIdx.x / ppl, d = 2 * ((int)blockIdx.x - m * ppl);
   const int g = m * D + d;
@@ -895,11 +891,7 @@ __global__ __launch_bounds__(ColCfg<NS>::NT, ColCfg<NS>::MINB) void k_prompt_spe
     const float* __restrict__ X, float2* __restrict__ Hc, const float2* __restrict__ tw, int D) {
   constexpr int NT = ColCfg<NS>::NT, U = NS, N = 2 * NS, SH = ColCfg<NS>::SH;
   __shared__ float2 buf[ColCfg<NS>::SLOTS];
-  __shared__ float2 twl[NS / 64 + 64];
-  for (int j = (int)threadIdx.x; j < NS / 64; j += NT) twl[j] = tw[NS + 64 * j];
-  for (int l = (int)threadIdx.x; l < 64; l += NT) twl[NS / 64 + l] = tw[NS + l];
-  const TwSplit<NS> twz{twl, twl + NS / 64};
-  constexpr int CC = NS / 16;
+  const fft::TwGlobal twz{tw};
   const int ppl = (D + 1) / 2;  // pairs per layer
   const int m = (int)blockIdx.x / ppl, d = 2 * ((int)blockIdx.x - m * ppl);
   const int g = m * D + d;
@@ -907,7 +899,7 @@ __global__ __launch_bounds__(ColCfg<NS>::NT, ColCfg<NS>::MINB) void k_prompt_spe
   const float* xa = X + (size_t)g * U;
   fft::forward_from_global<NS, 1, 1, NT, false, SH>(buf, twz, [&](int row, int) -> float2 {
     const float2 v = make_float2(xa[row], hasb ? xa[U + row] : 0.f);
-    if constexpr (PAR == 1) return cmul(v, cmul(tw[N + (row & (CC - 1))], tw[32 + row / CC]));
+    if constexpr (PAR == 1) return cmul(v, tw[N + row]);
     return v;
   });
   float2* ha = Hc + (size_t)g * (U + 1);
