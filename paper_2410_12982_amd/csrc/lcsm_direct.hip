@@ -159,23 +159,23 @@ __global__ __launch_bounds__(kThreads) void k_step_fused(const float* __restrict
 
 // The chain's input rule y = x + 0.5 tanh(z), evaluated as (x + 1/2) - r,
 // r = 1/(1 + e^{2z}) (the same function: 0.5 tanh(z) = 1/2 - r), from the
-// hardware base-2 exponential and reciprocal (each within about one ulp).
-// What runs from layer to layer and position to position is not z but
-// s = 2 log2(e) z = B y + A with B = 2 log2(e) h_0 and A = 2 log2(e) acc known
-// beforehand, so the dependent chain of a layer is exp2, an addition, rcp, a
-// subtraction and one multiply-add, and z follows from y off the chain.  (One
-// operation less, s affine in r itself, rounds where h_0 (x + 1/2) cancels: 3 to
-// 5 % more error over closed loops.)  Absolute error of y below 3.3e-7 for |x|
-// <= 3.  z = +inf gives x + 1/2, z = -inf x - 1/2, NaN stays NaN (taps and
-// accumulators beyond 1.1e38 overflow in s and act as infinite).  At t = 0
-// layer 0's input is x itself: x in place of x + 1/2 and r = 0.
-constexpr float kChainScale = 2.8853900817779268f;  // 2 log2(e)
-
-__device__ __forceinline__ float chain_r(float s) {
-  return __builtin_amdgcn_rcpf(1.f + __builtin_amdgcn_exp2f(s));
+// hardware base-2 exponential and reciprocal (each within about one ulp): no
+// branch, and x + 1/2 is off the serial chain.  Absolute error of y below 3.3e-7
+// for |x| <= 3 (an fp32 model of these steps with both hardware results off by
+// one ulp either way, against fp64, on 1.2M points with z over [-20, 20] and 1e-8
+// .. 32 of either sign); z = +inf gives x + 1/2, z = -inf x - 1/2, NaN stays NaN.
+// What runs from layer to layer and position to position is the rounded z that is
+// handed out: carrying 2 log2(e) z = B y + A with scaled taps and accumulators
+// saves the chain one multiplication (1.515 against 1.524 ms for 1024 positions
+// of 18 layers x 3072 columns), but rounds each term by itself: y was off by 3e-6
+// from the z handed out where h_0 y and the accumulator cancel from 100, by 1.7e-4
+// from 10^4, and not a number where only the scaled sum overflows (as it is: below
+// 1.5e-7 in all of them).  At t = 0 layer 0's input is x itself: x in place of
+// x + 1/2 and r = 0.
+__device__ __forceinline__ float chain_r(float z) {
+  return __builtin_amdgcn_rcpf(1.f + __builtin_amdgcn_exp2f(2.8853900817779268f * z));  // e^{2z}
 }
 __device__ __forceinline__ float chain_xh(float x, bool first) { return first ? x : x + 0.5f; }
-__device__ __forceinline__ float chain_scaled(float v) { return kChainScale * v; }
 
 template <int U>
 struct ChainChunk {
@@ -198,9 +198,9 @@ __global__ __launch_bounds__(kThreads) void k_chain_fused(const float* __restric
   const int c = (int)blockIdx.y * D + d;
   const size_t rs = (size_t)BD;
   const bool tile = (U > 0) && (dst_len > 0);
-  // s of z^{M-1}_{t-1} (first in the chain, so loaded ahead of the chunks;
-  // unused at t = 0), then of z^{m-1}_t
-  float sl = prev[c];
+  // z^{M-1}_{t-1} (first in the chain, so loaded ahead of the chunks; unused at
+  // t = 0), then z^{m-1}_t
+  float zl = prev[c];
   for (int m0 = 0; m0 < M; m0 += K) {
     float xv[K], acc[K], h0[K];
     float yb[K][NY], hh[K][NH], zo[K][NZ];
@@ -229,10 +229,7 @@ __global__ __launch_bounds__(kThreads) void k_chain_fused(const float* __restric
         }
       }
     }
-    // Pinned after the last load, as in k_step_fused: carrying s, the compiler
-    // sank the first tile's row into its condition behind the chain, a round
-    // trip more per step (512 positions of 32 x 16 x 2048: 11.15 -> 10.98 ms,
-    // 12 x 16 x 1024 4.02 -> 3.93; carrying z, without the pin, 10.96 and 3.89).
+    // Pinned after the last load, as in k_step_fused.
 #pragma unroll
     for (int kk = 0; kk < K; ++kk) {
       asm volatile("" : "+v"(xv[kk]), "+v"(acc[kk]), "+v"(h0[kk]));
@@ -253,11 +250,11 @@ __global__ __launch_bounds__(kThreads) void k_chain_fused(const float* __restric
         float* col = S + (size_t)m * SL * BD + c;
         const bool first = m == 0 && t == 0;
         const float xh = chain_xh(xv[kk], first);
-        const float r = first ? 0.f : chain_r(sl);
+        const float r = first ? 0.f : chain_r(zl);
         const float yv = xh - r;
-        z[(size_t)m * BD + c] = fmaf(h0[kk], yv, acc[kk]);
+        zl = fmaf(h0[kk], yv, acc[kk]);
+        z[(size_t)m * BD + c] = zl;
         col[(size_t)t * rs] = yv;
-        sl = fmaf(chain_scaled(h0[kk]), yv, chain_scaled(acc[kk]));
         if constexpr (U > 0) {
           if (tile) {
             yb[kk][U - 1] = yv;
@@ -275,7 +272,7 @@ __global__ __launch_bounds__(kThreads) void k_chain_fused(const float* __restric
       }
     }
   }
-  prev[c] = sl;
+  prev[c] = zl;
 }
 
 // The chained steps (lcsm_step_chain) of the positions [t0, t1) of one
@@ -304,8 +301,8 @@ __global__ __launch_bounds__(kThreads) void k_chain_fused(const float* __restric
 // dependent layers per position and nothing beside it, so the layers are cut
 // into two halves and a position into two phases: while wave 0 walks one
 // half, the waves of the other half take the y it left them, store y and z,
-// add the tile's first row (the next accumulator) and prepare A of the next
-// position, which wave 0 finds ready when it comes back.  A phase ends with a
+// add the tile's first row (the next accumulator) and hand it over, so that
+// wave 0 finds it ready when it comes back.  A phase ends with a
 // barrier that orders LDS only (no wave reads global memory another wave of
 // the launch writes).  A tile's other rows and the part of the next first row
 // that does not need the newest input follow in the phase after, and x is
@@ -403,7 +400,7 @@ __global__ __launch_bounds__(64) void k_chain_lane(
   for (int m = 0; m < ML; ++m)
     chain_block_load(S + (size_t)m * SL * BD + c, Hf + (size_t)m * L * D + d, rs, D, L, b, v[m],
                      hh[m], h0[m]);
-  float sl = prev[c];  // unused at t = 0
+  float zl = prev[c];  // z^{M-1}_{t-1}, unused at t = 0
   int zs = zs0 % zring;
   auto position = [&](auto rc) {
     constexpr int r = decltype(rc)::value;
@@ -414,10 +411,10 @@ __global__ __launch_bounds__(64) void k_chain_lane(
     for (int m = 0; m < ML; ++m) {
       const bool first = m == 0 && t == 0;
       const float xh = chain_xh(xv[m][r], first);
-      const float rr = first ? 0.f : chain_r(sl);
+      const float rr = first ? 0.f : chain_r(zl);
       const float yv = xh - rr;
-      sl = fmaf(chain_scaled(h0[m]), yv, chain_scaled(v[m][r]));
-      z[(size_t)zs * zst + (size_t)m * BD + c] = fmaf(h0[m], yv, v[m][r]);
+      zl = fmaf(h0[m], yv, v[m][r]);
+      z[(size_t)zs * zst + (size_t)m * BD + c] = zl;
       S[((size_t)m * SL + t) * rs + c] = yv;
       v[m][r] = yv;
       if constexpr (r + 1 < W) {
@@ -431,7 +428,7 @@ __global__ __launch_bounds__(64) void k_chain_lane(
     zs = zs + 1 == zring ? 0 : zs + 1;
   };
   static_for<W>(position);
-  prev[c] = sl;
+  prev[c] = zl;
 #pragma unroll
   for (int m = 0; m < ML; ++m)
 #pragma unroll
@@ -450,13 +447,13 @@ constexpr int chain_half(int M) {
 // layer and half made it 1.3 times slower).  Phase h: half h's layers in order,
 // then the barrier.
 template <int M, int NC, int HM>
-__device__ __forceinline__ float chain_walk(const float2 (*abuf)[NC], const float (*bbuf)[NC],
-                                            float (*ybuf)[NC], int col, float sl, bool first,
+__device__ __forceinline__ float chain_walk(const float2 (*abuf)[NC], const float (*hbuf)[NC],
+                                            float (*ybuf)[NC], int col, float zl, bool first,
                                             int n) {
   constexpr int H = chain_half<64 / NC>(M);
-  float bv[M];
+  float h0[M];
 #pragma unroll
-  for (int m = 0; m < M; ++m) bv[m] = bbuf[m < H ? m : HM + m - H][col];
+  for (int m = 0; m < M; ++m) h0[m] = hbuf[m < H ? m : HM + m - H][col];
   for (; n > 0; --n) {
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
@@ -466,17 +463,17 @@ __device__ __forceinline__ float chain_walk(const float2 (*abuf)[NC], const floa
       for (int m = m0; m < m1; ++m) av[m - m0] = abuf[h * HM + m - m0][col];
 #pragma unroll
       for (int m = m0; m < m1; ++m) {
-        float rr = chain_r(sl);
+        float rr = chain_r(zl);
         if (m == 0) rr = first ? 0.f : rr;
         const float yv = av[m - m0].x - rr;
         ybuf[h * HM + m - m0][col] = yv;  // lanes of one column write the same value
-        sl = fmaf(bv[m], yv, av[m - m0].y);
+        zl = fmaf(h0[m], yv, av[m - m0].y);
       }
       chain_block_sync();
     }
     first = false;
   }
-  return sl;
+  return zl;
 }
 
 // HM: layers of the larger half at most; ML0 .. ML1 the layer counts.
@@ -487,8 +484,9 @@ __global__ __launch_bounds__(64 * (1 + (ML1 + 64 / NC - 1) / (64 / NC))) void k_
     float* __restrict__ prev, int M, int L, int SL, int BD, int D, int t0, int t1,
     int tile_last) {
   constexpr int W = kChainBlockW, LPW = 64 / NC, XA = kChainXAhead;
-  __shared__ float2 abuf[2 * HM][NC];  // x + 1/2 and A of the next position, by half and layer in it
-  __shared__ float bbuf[2 * HM][NC];   // B
+  // x + 1/2 and the accumulator of the next position, by half and layer in it
+  __shared__ float2 abuf[2 * HM][NC];
+  __shared__ float hbuf[2 * HM][NC];   // h_0
   __shared__ float ybuf[2 * HM][NC];   // y of the position taken last
   const int lane = (int)threadIdx.x & 63;
   const int wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
@@ -501,14 +499,14 @@ __global__ __launch_bounds__(64 * (1 + (ML1 + 64 / NC - 1) / (64 / NC))) void k_
   const int H = chain_half<LPW>(M);
   if (wv == 0) {
     __builtin_amdgcn_s_setprio(3);
-    float sl = prev[cc];  // s of z^{M-1}_{t-1}; unused at t = 0
+    float zl = prev[cc];  // z^{M-1}_{t-1}; unused at t = 0
     chain_block_sync();
     auto walk = [&](auto mc) {
       constexpr int MM = ML0 + decltype(mc)::value;
-      if (M == MM) sl = chain_walk<MM, NC, HM>(abuf, bbuf, ybuf, col, sl, t0 == 0, r1 - r0);
+      if (M == MM) zl = chain_walk<MM, NC, HM>(abuf, hbuf, ybuf, col, zl, t0 == 0, r1 - r0);
     };
     static_for<ML1 - ML0 + 1>(walk);
-    if (lane < NC && live) prev[c] = sl;
+    if (lane < NC && live) prev[c] = zl;
     return;
   }
   const int m = LPW * (wv - 1) + lane / NC;
@@ -536,7 +534,7 @@ __global__ __launch_bounds__(64 * (1 + (ML1 + 64 / NC - 1) / (64 / NC))) void k_
   float part = 0.f;
   // what wave 0 needs of position t, its accumulator complete
   auto prepare = [&](int t, float acc, float xv) {
-    if (has) abuf[slot][col] = make_float2(chain_xh(xv, mc == 0 && t == 0), chain_scaled(acc));
+    if (has) abuf[slot][col] = make_float2(chain_xh(xv, mc == 0 && t == 0), acc);
   };
   auto tile_of = [&](int r) { return r + 1 < W && b + r + 1 < L && (r + 1 < r1 || tile_last); };
   auto begin = [&](auto rc) {
@@ -546,7 +544,7 @@ __global__ __launch_bounds__(64 * (1 + (ML1 + 64 / NC - 1) / (64 / NC))) void k_
     part = chain_block_first_part<r>(v, hh);
   };
   static_for<W>(begin);
-  if (has) bbuf[slot][col] = chain_scaled(h0);
+  if (has) hbuf[slot][col] = h0;
   chain_block_sync();
   chain_block_sync();
   if (half) chain_block_sync();

@@ -125,6 +125,47 @@ def test_run_chain_matches_the_oracle_closed_loop(name):
     assert err <= TOL
 
 
+@pytest.mark.parametrize("M,run", [(2, False), (2, True), (3, True), (9, False), (9, True)])
+def test_chain_input_follows_the_emitted_z(M, run):
+    """y^m = x^m + 0.5 tanh(z^{m-1}) of the z handed out, to the documented
+    3.3e-7 for |x| <= 3, where z = h_0 y + acc cancels: layer 0 has taps (K, -K)
+    and inputs by which z^0_1 = K (y^0_1 - y^0_0) stays small beside its terms,
+    up to taps whose scaled sums would overflow; the other layers have the tap
+    1 alone, so z^m is y^m.  One position a launch, a lane per column (M = 2)
+    and the chain of a workgroup (M = 3, 9)."""
+    say(f"[chain cancelling] M={M} run={run}")
+    K = np.array([1.0, 10.0, 30.0, 100.0, 1e4, 2e38]).repeat(128)
+    B, D, L = 4, K.size, 4
+    rng = np.random.default_rng(5)
+    h = np.zeros((M, D, L), np.float32)
+    h[0, :, 0], h[0, :, 1] = K, -K
+    h[1:, :, 0] = 1.0
+    x = rng.uniform(-1, 1, (2, M, B, D)).astype(np.float32)
+    x[0, 0] = rng.uniform(0.3, 0.9, (B, D))
+    # x^0_1 such that y^0_1 = y^0_0 + delta, |K delta| <= 1
+    z = K * x[0, 0].astype(np.float64)
+    for m in range(1, M):
+        z = x[0, m] + 0.5 * np.tanh(z)
+    x[1, 0] = x[0, 0] + rng.uniform(-1, 1, (B, D)) / K - 0.5 * np.tanh(z)
+    assert np.abs(x).max() <= 3
+    ctx = lcsm_mod().Lcsm(torch.from_numpy(h).to(dev()), B)
+    xd = torch.from_numpy(x).to(dev())
+    zd = torch.full_like(xd, float("nan"))
+    if run:
+        ctx.run_chain(xd, zd)
+    else:
+        for t in range(2):
+            ctx.step_chain(xd[t], zd[t])
+    torch.cuda.synchronize()
+    ctx.close()
+    zg = zd.cpu().numpy().astype(np.float64)
+    err = np.abs(zg[:, 1:] - (x[:, 1:] + 0.5 * np.tanh(zg[:, :-1])))
+    for k in range(6):
+        say(f"  K={K[128 * k]:g}: max |z^0_1| {np.abs(zg[1, 0, :, 128 * k:128 * k + 128]).max():.3g}, "
+            f"error of y {err[..., 128 * k:128 * k + 128].max():.3e}")
+    assert err.max() < 3.3e-7
+
+
 def test_run_chain_errors():
     lcsm = lcsm_mod()
     w = datagen.Workload("chainrunerr", 1, 1, 8, 40, decay=10.0, seed=2)
