@@ -198,9 +198,7 @@ __global__ __launch_bounds__(kThreads) void k_chain_fused(const float* __restric
   const int c = (int)blockIdx.y * D + d;
   const size_t rs = (size_t)BD;
   const bool tile = (U > 0) && (dst_len > 0);
-  // z^{M-1}_{t-1} (first in the chain, so loaded ahead of the chunks; unused at
-  // t = 0), then z^{m-1}_t
-  float zl = prev[c];
+  float zl = 0.f;  // z^{M-1}_{t-1} (loaded with the first chunk), then z^{m-1}_t
   for (int m0 = 0; m0 < M; m0 += K) {
     float xv[K], acc[K], h0[K];
     float yb[K][NY], hh[K][NH], zo[K][NZ];
@@ -229,29 +227,14 @@ __global__ __launch_bounds__(kThreads) void k_chain_fused(const float* __restric
         }
       }
     }
-    // Pinned after the last load, as in k_step_fused.
-#pragma unroll
-    for (int kk = 0; kk < K; ++kk) {
-      asm volatile("" : "+v"(xv[kk]), "+v"(acc[kk]), "+v"(h0[kk]));
-      if constexpr (U > 0) {
-#pragma unroll
-        for (int k = 0; k < U - 1; ++k) asm volatile("" : "+v"(yb[kk][k]));
-#pragma unroll
-        for (int l = 1; l < 2 * U; ++l) asm volatile("" : "+v"(hh[kk][l]));
-#pragma unroll
-        for (int j = 0; j < U; ++j) asm volatile("" : "+v"(zo[kk][j]));
-      }
-    }
+    if (m0 == 0) zl = prev[c];  // unused at t = 0
     // the chain through the chunk, then its stores
 #pragma unroll
     for (int kk = 0; kk < K; ++kk) {
       const int m = m0 + kk;
       if (m < M) {
         float* col = S + (size_t)m * SL * BD + c;
-        const bool first = m == 0 && t == 0;
-        const float xh = chain_xh(xv[kk], first);
-        const float r = first ? 0.f : chain_r(zl);
-        const float yv = xh - r;
+        const float yv = (m == 0 && t == 0) ? xv[kk] : (xv[kk] + 0.5f) - chain_r(zl);
         zl = fmaf(h0[kk], yv, acc[kk]);
         z[(size_t)m * BD + c] = zl;
         col[(size_t)t * rs] = yv;
