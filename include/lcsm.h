@@ -209,7 +209,8 @@ int lcsm_run(lcsm_ctx* ctx, int n, const float* y, size_t y_stride, float* z, si
  * full-state storage, at most 30 layers and at most 8192 columns per layer
  * (B*D), every stretch of such positions runs as one launch that keeps each
  * column's block rows in registers, and only the larger tiles are launched
- * on their own.  Other shapes take one position at a time.  Errors as
+ * on their own.  Other shapes take one position at a time, and so do
+ * stretches in which a step's x slab is an earlier one's z slab.  Errors as
  * lcsm_step_chain; stops at the first. */
 int lcsm_run_chain(lcsm_ctx* ctx, int n, const float* x, size_t x_stride, float* z,
                    size_t z_stride);

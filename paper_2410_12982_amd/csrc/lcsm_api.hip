@@ -492,6 +492,23 @@ bool chain_block_fits(const lcsm_ctx* c) {
   return !c->T && c->s.M <= lcsm::kChainBlockMaxM && groups <= lcsm::kChainBlockMaxGroups;
 }
 
+// Whether one of n <= kChainBlockW consecutive steps writes a z slab that a later
+// one of them reads as its x (a program may feed outputs back as inputs, or share
+// a ring).  The block launch loads x ahead of the z before it, so such a stretch
+// takes one position at a time.
+bool chain_reads_back(int n, const float* x, size_t xst, int xring, int xs, const float* z,
+                      size_t zst, int zring, int zs, size_t slab) {
+  const uintptr_t bytes = sizeof(float) * slab;
+  uintptr_t xa[lcsm::kChainBlockW];
+  for (int k = 0; k < n; ++k) xa[k] = (uintptr_t)x + sizeof(float) * xst * ((xs + k) % xring);
+  for (int k = 0; k < n; ++k) {
+    const uintptr_t za = (uintptr_t)z + sizeof(float) * zst * ((zs + k) % zring);
+    for (int j = k + 1; j < n; ++j)
+      if (za < xa[j] + bytes && xa[j] < za + bytes) return true;
+  }
+  return false;
+}
+
 int chain_run(lcsm_ctx* c, int n, const float* x, size_t xst, int xring, int xs0, float* z,
               size_t zst, int zring, int zs0) {
   if (!c) return LCSM_EINVAL;
@@ -500,6 +517,11 @@ int chain_run(lcsm_ctx* c, int n, const float* x, size_t xst, int xring, int xs0
   if (c->layers_done != 0) return fail(c, LCSM_ESTATE, "step during a per-layer position", hipSuccess);
   const bool block = chain_block_fits(c);
   constexpr int W = lcsm::kChainBlockW;
+  const size_t slab = (size_t)c->s.M * c->s.BD;
+  // the slabs of x and z lie in ranges that meet (only then are they compared)
+  const uintptr_t xe = (uintptr_t)x + sizeof(float) * (xst * (size_t)(xring - 1) + slab);
+  const uintptr_t ze = (uintptr_t)z + sizeof(float) * (zst * (size_t)(zring - 1) + slab);
+  const bool meet = (uintptr_t)x < ze && (uintptr_t)z < xe;
   int k = 0;
   while (k < n) {
     if (c->t >= c->s.L) return LCSM_EDONE;
@@ -524,6 +546,15 @@ int chain_run(lcsm_ctx* c, int n, const float* x, size_t xst, int xring, int xs0
         tile_last = false;
         break;
       }
+    }
+    if (meet && chain_reads_back(t1 - t0, x, xst, xring, (xs0 + k) % xring, z, zst, zring,
+                                 (zs0 + k) % zring, slab)) {
+      for (; c->t < t1; ++k) {
+        const int r = step_common(c, x + (size_t)((xs0 + k) % xring) * xst,
+                                  z + (size_t)((zs0 + k) % zring) * zst, true);
+        if (r) return r;
+      }
+      continue;
     }
     hipError_t e = lcsm::launch_chain_block(x, xst, xring, (xs0 + k) % xring, z, zst, zring,
                                             (zs0 + k) % zring, c->S, c->Hf, c->prev, c->s, t0, t1,

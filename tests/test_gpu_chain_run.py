@@ -166,6 +166,54 @@ def test_chain_input_follows_the_emitted_z(M, run):
     assert err.max() < 3.3e-7
 
 
+@pytest.mark.parametrize("M", [1, 2, 3, 9])
+@pytest.mark.parametrize("ahead", [1, 2, 5, 31, 32, -1, 0])
+def test_run_chain_reads_back_its_outputs(M, ahead):
+    """x_{k+ahead} is z_k (one buffer, z `ahead` slabs behind x): the block
+    launch loads x ahead, so it may not take such positions.  The loop of single
+    steps is the reference; ahead <= 0 overwrites inputs already read."""
+    say(f"[run_chain reads back] M={M} ahead={ahead}")
+    B, D, L = 2, 40, 100
+    w = datagen.Workload("chainback", M, B, D, L, decay=8.0, seed=M + ahead)
+    ctx = lcsm_mod().Lcsm(datagen.filters_torch(w, dev()) * 0.1, B)
+    slab, lead = M * B * D, max(0, -ahead)
+    x0 = torch.rand((L + 32, M, B, D), device=dev()) - 0.5
+    want, got = x0.clone(), x0.clone()
+    xs, zs = 4 * slab * lead, 4 * slab * (lead + ahead)
+    lib = lcsm_mod().raw()
+    for t in range(L):
+        p = want.data_ptr() + 4 * slab * t
+        assert lib.lcsm_step_chain(ctx._ctx, p + xs, p + zs) == 0
+    ctx.reset()
+    assert lib.lcsm_run_chain(ctx._ctx, L, got.data_ptr() + xs, slab, got.data_ptr() + zs, slab) == 0
+    torch.cuda.synchronize()
+    assert torch.isfinite(want).all()
+    assert torch.equal(got, want)
+    ctx.close()
+
+
+@pytest.mark.parametrize("M,ring", [(1, 3), (2, 31), (9, 1), (9, 3), (9, 40)])
+def test_recorded_chain_on_one_ring(M, ring):
+    """A recorded run whose x and z are one ring: step k reads what step k - ring
+    wrote."""
+    say(f"[run_chain ring] M={M} ring={ring}")
+    B, D, L = 2, 40, 100
+    w = datagen.Workload("chainring", M, B, D, L, decay=8.0, seed=M + ring)
+    st = torch.cuda.Stream()
+    with torch.cuda.stream(st):
+        ctx = lcsm_mod().Lcsm(datagen.filters_torch(w, dev()) * 0.1, B)
+        x0 = torch.rand((ring, M, B, D), device=dev()) - 0.5
+        want, got = x0.clone(), x0.clone()
+        for t in range(L):
+            ctx.step_chain(want[t % ring], want[t % ring])
+        g = ctx.capture(got, got, n=L, chain=True)
+        g.launch()
+    torch.cuda.synchronize()
+    assert torch.isfinite(want).all()
+    assert torch.equal(got, want)
+    ctx.close()
+
+
 def test_run_chain_errors():
     lcsm = lcsm_mod()
     w = datagen.Workload("chainrunerr", 1, 1, 8, 40, decay=10.0, seed=2)
