@@ -45,12 +45,12 @@ typedef struct lcsm_synth lcsm_synth;
  *   w_down   device [M][D][2D] ([out][in]);  b_down  device [M][D].
  * All five are copied during the call's stream work; the caller may free
  * them once the stream has passed lcsm_synth_init.  D must be a multiple of
- * 4 (16-byte weight rows).  opt is passed to the mixer (lcsm_options,
- * NULL for the defaults).  The library allocates its device memory (the
- * mixer's workspace, a copy of the weights, M*(4D*D + 3D) floats, and
- * 3 B' D + B D floats of buffers, B' the batch rounded up to 4).  Errors: LCSM_EINVAL (null pointers, D not a
- * multiple of 4, or what lcsm_init rejects), LCSM_ENOMEM, LCSM_EDEVICE;
- * *out is NULL on failure. */
+ * 4; the pointers need no more than a float's alignment.  opt is passed to the
+ * mixer (lcsm_options, NULL for the defaults).  The library allocates its
+ * device memory (the mixer's workspace, a copy of the weights, M*(4D*D + 3D)
+ * floats, and 3 B' D + B D floats of buffers, B' the batch rounded up to 4).
+ * Errors: LCSM_EINVAL (null pointers, D not a multiple of 4, or what lcsm_init
+ * rejects), LCSM_ENOMEM, LCSM_EDEVICE; *out is NULL on failure. */
 int lcsm_synth_init(lcsm_synth** out, const float* filters, const float* w_up, const float* b_up,
                     const float* w_down, const float* b_down, int M, int B, int D, int L,
                     void* stream, const lcsm_options* opt);

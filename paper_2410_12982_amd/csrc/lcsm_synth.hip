@@ -235,14 +235,16 @@ __global__ __launch_bounds__(kProdMaxThreads) void k_prod(const float* __restric
 }
 
 // dst = src [rows][K] in the quad layout (rows and K multiples of 4), one
-// thread per four values of a row.
+// thread per four values of a row.  src is the caller's: aligned as a float is.
+typedef float v4f_any __attribute__((ext_vector_type(4), aligned(4)));
+
 __global__ __launch_bounds__(256) void k_quads(const float* __restrict__ src,
                                                float* __restrict__ dst, size_t rows, int K) {
   const size_t n = rows * (size_t)(K / 4), step = (size_t)gridDim.x * 256;
   for (size_t q = (size_t)blockIdx.x * 256 + threadIdx.x; q < n; q += step) {
     // q counts the destination's quads: [row / 4][k / 4][row % 4]
     const size_t g = q / K, r = q - g * K;  // K quads per four rows
-    const v4f v = *reinterpret_cast<const v4f*>(src + (4 * g + (r & 3)) * K + (r & ~(size_t)3));
+    const v4f v = *reinterpret_cast<const v4f_any*>(src + (4 * g + (r & 3)) * K + (r & ~(size_t)3));
     *reinterpret_cast<v4f*>(dst + 4 * q) = v;
   }
 }

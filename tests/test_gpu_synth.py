@@ -92,6 +92,28 @@ def test_synth_product_edges(B, D):
     assert err <= bound
 
 
+@pytest.mark.parametrize("off", [1, 2, 3])
+def test_synth_weights_at_any_float_address(off):
+    """Filters and weights that start `off` floats into an allocation (views of a
+    larger tensor) give the bits of aligned ones."""
+    B, D, L = 3, 68, 20
+    say(f"[synth weights at an offset] {off}")
+    w = datagen.Workload("synth_off", 2, B, D, L, decay=8.0, seed=70)
+    eps = datagen.noise_torch(w, dev())
+    h, ws = datagen.filters_torch(w, dev()), datagen.mlp_weights_torch(w, dev())
+
+    def moved(t):
+        big = torch.zeros(t.numel() + off, device=dev())
+        v = big[off:].view(t.shape)
+        v.copy_(t)
+        assert v.data_ptr() % 16 == 4 * off and v.is_contiguous()
+        return v
+
+    want = _gpu_run(_make(w, h, ws), eps, L)
+    got = _gpu_run(_make(w, moved(h), tuple(moved(t) for t in ws)), eps, L)
+    assert np.array_equal(got, want)
+
+
 def test_synth_identity_blocks():
     """W_up = [I; -I], W_down = [I, -I], no biases: each block is the identity
     (gelu(x) - gelu(-x) = x) and the model is linear in the noise."""
