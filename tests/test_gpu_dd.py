@@ -20,7 +20,7 @@ import pytest
 import torch
 
 import datagen
-from oracle.dd import relaxed_dd
+from oracle.dd import dd_tiles_after_step, relaxed_dd
 
 from gpu_harness import TOL, dev, lcsm_mod, rel_err, say
 
@@ -189,6 +189,47 @@ def test_dd_wide_steps(L, dmax):
         assert np.abs(zg - ref[:L]).max() < 0.25
         zg = np.rint(zg)
     assert np.array_equal(zg.astype(np.int64), ref[:L])
+
+
+@pytest.mark.parametrize("L", [64, 128])
+def test_dd_wide_steps_keep_the_tiles_sums_apart(L):
+    """Rounding of the steps with tiles of 16 and 32: no further from 64 bits than
+    an fp32 run on the host in which every tile is a sum of its own (fused
+    multiply-adds in the order of its fixed rows), added to its destination tile
+    by tile.  One long sum over all tiles of a step is about 11 % further off; the
+    2-norms run over 4096 columns, so two of like errors agree to below 1 %."""
+    C = 4096
+    w = datagen.Workload("dd_apart", 1, 1, C, L, decay=L / 8, seed=5)
+    say(f"[dd tile sums] L={L}")
+    y, rho = datagen.y_torch(w, dev()), datagen.rho_torch(w, dev())
+    ctx = lcsm_mod().Dd(1, 1, C, L)
+    zg = _run(ctx, y, rho).reshape(L, C).astype(np.float64)
+    ctx.close()
+    ys, rs = y.cpu().numpy().reshape(L, C), rho.cpu().numpy().reshape(L, C)
+    y64, r64 = ys.astype(np.float64), rs.astype(np.float64)
+
+    def fma(a, b, c):  # on fp32 rows: the product of two fp32 is exact in fp64
+        return (a.astype(np.float64) * b + c).astype(np.float32)
+
+    exact = np.zeros((2 * L - 1, C))
+    for j in range(L):
+        exact[j:j + L] += y64[j] * r64
+    exact = exact[:L]
+    acc = np.zeros((L, C), np.float32)
+    zh = np.zeros((L, C), np.float32)
+    for t in range(L):
+        zh[t] = fma(ys[t], rs[0], fma(ys[0], rs[t], acc[t])) if t else fma(ys[0], rs[0], acc[0])
+        for kind, U, lo, d0, d1 in dd_tiles_after_step(t, L):
+            for j in range(d1 - d0):
+                s = np.zeros(C, np.float32)
+                for k in range(max(0, j - U + 1), min(U, j + 1)):
+                    s = fma(ys[U + k], rs[lo + j - k], s)
+                    if kind == "rect":
+                        s = fma(rs[U + k], ys[lo + j - k], s)
+                acc[d0 + j] += s
+    err = [float(np.linalg.norm(z - exact) / np.linalg.norm(exact)) for z in (zg, zh)]
+    say(f"  error: device {err[0]:.4e}, host fp32 {err[1]:.4e}")
+    assert err[0] <= 1.02 * err[1]
 
 
 @pytest.mark.parametrize("BD", [1 << 17, (1 << 17) + 5, (1 << 17) + 31])
