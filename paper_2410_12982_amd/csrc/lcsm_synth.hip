@@ -281,8 +281,12 @@ hipError_t prod_rows(const float* x, const float* W, const float* bias, float* o
   const bool two = N >= 6 * kProdCus;
   const int nch = (K + 63) / 64, outs = 16 * RG * (two ? 2 : 1);
   // at most 16 waves, chunks shared evenly; 8 for the long rows, whose 16
-  // waves only compete (16 rows, 4096 x 2048: 10.3 against 11.4 us)
-  const int most = nch <= 24 ? kProdMaxThreads / 64 : 8;
+  // waves only compete (16 rows, 4096 x 2048: 10.3 against 11.4 us).  One row
+  // takes 16 throughout: a model of 18 layers, 1024 channels, one row 149.1 us per
+  // position against 159.4 with 8 (158.6 with a unit's row per workgroup on the
+  // vector ALU), 2048 channels 283.6 against 291.9, 8 layers of 1024 channels,
+  // whose weights stay in the caches, 61.8 against 61.6
+  const int most = nch <= 24 || nrows == 1 ? kProdMaxThreads / 64 : 8;
   const int rounds = (nch + most - 1) / most;
   int threads = 64 * ((nch + rounds - 1) / rounds);
   if (threads < outs) threads = (outs + 63) / 64 * 64;  // a thread per output

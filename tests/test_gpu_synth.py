@@ -74,7 +74,8 @@ def test_synth_matches_oracle(shape):
     assert err <= TOL
 
 
-@pytest.mark.parametrize("B,D", [(1, 772), (4, 768), (5, 4), (6, 1540), (11, 64), (16, 260), (13, 768)])
+@pytest.mark.parametrize("B,D", [(1, 772), (1, 1028), (4, 768), (5, 4), (6, 1540), (11, 64), (16, 260),
+                                 (13, 768)])
 def test_synth_product_edges(B, D):
     """The block products at the edges of their tiles: 1 to 16 rows (a quad of
     rows whole and ragged), 4 and 8 units per workgroup (from 1536 units), rows
