@@ -386,7 +386,7 @@ __device__ __forceinline__ void first_pass_load(
 
 // First pass (index 0, p = 1, no twiddles) from registers into LDS;
 // synchronises at the end.
-template <int N, int WC, int LDSW, int NT, bool INV, bool HALF, int SH = 0>
+template <int N, int WC, int LDSW, int NT, bool INV, bool HALF>
 __device__ __forceinline__ void first_pass_regs(
     float2* buf, const typename FirstPass<N, WC, NT, HALF>::In& in) {
   using F = FirstPass<N, WC, NT, HALF>;
@@ -400,9 +400,45 @@ __device__ __forceinline__ void first_pass_regs(
 #pragma unroll
       for (int q = 0; q < R; ++q) v[q] = (q < F::QIN) ? in[a][q < F::QIN ? q : 0] : make_float2(0.f, 0.f);
       dft<R, INV>(v);
+#pragma unroll
+      for (int s = 0; s < R; ++s) buf[(j * R + s) * LDSW + col] = v[s];
+    }
+  }
+  __syncthreads();
+}
+
+// First pass with inputs fetched by load(row, col) instead of from LDS; only
+// rows < N*QIN/R are fetched (the rest are zero: QIN = R/2 for a zero-padded
+// upper half, R for full input).  Writes its outputs to LDS and synchronises.
+// One body, and not first_pass_load and first_pass_regs in turn: through a second
+// array the tile kernels take two registers more, at 2U = 1024 and odd column
+// counts the step from two workgroups per CU to one (12 x 3 x 515 columns: 55.3
+// -> 72.4 us).
+template <int N, int WC, int LDSW, int NT, bool INV, bool HALF, int SH = 0, class Load>
+__device__ __forceinline__ void first_pass_global(float2* buf, const Load& load) {
+  constexpr int R = Plan<N>::radix(0);
+  constexpr int QIN = HALF ? R / 2 : R;
+  constexpr int UNITS = N / R * WC;
+  constexpr int UPT = (UNITS + NT - 1) / NT;
+  float2 v[UPT][R];
+#pragma unroll
+  for (int a = 0; a < UPT; ++a) {
+    const int u = (int)threadIdx.x + a * NT;
+    if (UNITS % NT == 0 || u < UNITS) {
+      const int j = u / WC, col = u % WC;
+#pragma unroll
+      for (int q = 0; q < R; ++q) v[a][q] = (q < QIN) ? load(j + q * (N / R), col) : make_float2(0.f, 0.f);
+    }
+  }
+#pragma unroll
+  for (int a = 0; a < UPT; ++a) {
+    const int u = (int)threadIdx.x + a * NT;
+    if (UNITS % NT == 0 || u < UNITS) {
+      const int j = u / WC, col = u % WC;
+      dft<R, INV>(v[a]);
       if constexpr (SH == 0) {
 #pragma unroll
-        for (int s = 0; s < R; ++s) buf[(j * R + s) * LDSW + col] = v[s];
+        for (int s = 0; s < R; ++s) buf[(j * R + s) * LDSW + col] = v[a][s];
       } else {
         // one column only: j R is a multiple of R, so for s < R the slot of
         // j R + s is that of j R plus s plus the padding within s
@@ -411,24 +447,14 @@ __device__ __forceinline__ void first_pass_regs(
 #pragma unroll
         for (int s = 0; s < R; ++s) {
           if constexpr (R <= (1 << SH))
-            buf[b + s] = v[s];
+            buf[b + s] = v[a][s];
           else
-            buf[b + s + (s >> SH)] = v[s];
+            buf[b + s + (s >> SH)] = v[a][s];
         }
       }
     }
   }
   __syncthreads();
-}
-
-// First pass with inputs fetched by load(row, col) instead of from LDS; only
-// rows < N*QIN/R are fetched.  Writes its outputs to LDS and synchronises.
-template <int N, int WC, int LDSW, int NT, bool INV, bool HALF, int SH = 0, class Load>
-__device__ __forceinline__ void first_pass_global(float2* buf, const Load& load) {
-  using F = FirstPass<N, WC, NT, HALF>;
-  typename F::In in;
-  first_pass_load<N, WC, NT, HALF>(in, load);
-  first_pass_regs<N, WC, LDSW, NT, INV, HALF, SH>(buf, in);
 }
 
 // Last pass (index NP-1, p = N/R) reading LDS and handing the outputs of

@@ -59,3 +59,13 @@ def test_single_position_chain_keeps_its_waves(vgprs, U, K, waves):
     got = [v for n, v in vgprs.items() if f"k_chain_fusedILi{U}ELi{K}E" in n]
     assert len(got) == 1
     assert got[0] <= 512 // waves
+
+
+@pytest.mark.parametrize("N", [128, 256, 1024])
+def test_row_panel_tile_keeps_two_workgroups(vgprs, N):
+    """Every form of k_fft_tile<N> (whole and ragged panels, with and without the
+    red cell): at most 128 registers, the limit of four waves per SIMD, which at
+    2U = 1024 are two workgroups of 512 threads per compute unit."""
+    got = [v for n, v in vgprs.items() if f"k_fft_tileILi{N}ELb0E" in n or f"k_fft_tileILi{N}ELb1E" in n]
+    assert len(got) >= 4
+    assert max(got) <= 128
