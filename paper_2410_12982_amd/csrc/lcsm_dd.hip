@@ -817,11 +817,12 @@ int lcsm_dd_step(lcsm_dd* c, const float* y_t, const float* rho_t, float* z_t) {
          U *= 2)
       uf = U;
   const dim3 rgrid((unsigned)((c->BD + lcsm::kThreads - 1) / lcsm::kThreads), (unsigned)c->M);
+  const dim3 rblock(lcsm::step_threads(c->BD));
 #define LCSM_DD_STEP(UU)                                                                        \
-  hipLaunchKernelGGL((lcsm::k_dd_step<UU>), rgrid, dim3(lcsm::kThreads), 0, c->stream, y_t,    \
+  hipLaunchKernelGGL((lcsm::k_dd_step<UU>), rgrid, rblock, 0, c->stream, y_t,    \
                      rho_t, z_t, c->Y, c->R, c->L, c->BD, t)
 #define LCSM_DD_WIDE(UU)                                                                        \
-  hipLaunchKernelGGL((lcsm::k_dd_step_wide<UU>), rgrid, dim3(lcsm::kThreads), 0, c->stream, y_t, \
+  hipLaunchKernelGGL((lcsm::k_dd_step_wide<UU>), rgrid, rblock, 0, c->stream, y_t, \
                      rho_t, z_t, c->Y, c->R, c->L, c->BD, t)
   switch (uf) {
     case 0: LCSM_DD_STEP(0); break;

@@ -694,7 +694,7 @@ inline unsigned blocks_for(int64_t n) { return (unsigned)((n + kThreads - 1) / k
 template <bool RED>
 hipError_t dispatch_fused(int U, const float* y, float* z, float* S, const float* Hf,
                           const Shape& s, int t, int dst_len, hipStream_t st) {
-  const dim3 block(kThreads);
+  const dim3 block(step_threads(s.D));
   const size_t ls = (size_t)s.SL * s.BD, hls = (size_t)s.L * s.D;
   // with half-state storage S lies outside its allocation: integer arithmetic
   float* St = (float*)((uintptr_t)S + sizeof(float) * (size_t)t * s.BD);

@@ -41,6 +41,14 @@ constexpr int kChainFusedManyU = 1;
 // Output chunk of the generic direct tile kernel (U >= kDirectJ).
 constexpr int kDirectJ = 16;
 
+// Threads of a step launch's workgroups over n columns (n channels, or n
+// columns of data-dependent filters): the kernels' lanes past n load the last
+// column, so where one workgroup holds all n it has no more waves than they need
+// (with 256 always, 512 positions of 32 x 64 x 16 1.73 ms, 1024 of 17 x 16 x 25
+// 2.56; as it is 1.50 and 2.41; with such waves leaving first in the kernel 1.51
+// and 2.42, but 8192 of 1 x 8 x 768 19.97 instead of 19.85).
+inline unsigned step_threads(int n) { return n < 256 ? ((unsigned)n + 63) / 64 * 64 : 256; }
+
 // [M][D][L] -> [M][L][D]
 hipError_t launch_transpose_filters(const float* src, float* dst, const Shape& s, hipStream_t st);
 

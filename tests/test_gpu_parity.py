@@ -283,10 +283,10 @@ def test_integer_data_at_the_layer_and_batch_limits(opt, shape):
         assert np.array_equal(np.rint(z).astype(np.int64), ex)
 
 
-@pytest.mark.parametrize("D", [1, 63, 255, 256, 257, 513])
+@pytest.mark.parametrize("D", [1, 63, 64, 65, 192, 193, 255, 256, 257, 513])
 @pytest.mark.parametrize("L", [2, 3, 37, 64, 97])
 def test_step_edges_integer_exact(D, L):
-    """Step launches at the edges of their channel blocks (the lanes past D in
+    """Step launches at the edges of their waves and channel blocks (the lanes past D in
     the last one load column D - 1) and of the sequence (the last tile of every
     size whole, clipped, absent), steps and advance after per-layer red cells:
     bit for bit the int64 convolution (sums below 2^24)."""
