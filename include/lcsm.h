@@ -288,17 +288,19 @@ void lcsm_graph_destroy(lcsm_graph* g);
  *      (strides in floats, as for lcsm_run).
  * P must be a power of two with 2P <= L (2P <= T with half_state), and the
  * context at position 0 (after
- * lcsm_init or lcsm_reset).  Afterwards the context is at position P in
- * exactly the state P calls of lcsm_step would leave (state rows < P hold the
- * prompt, rows >= P its contributions from the gray tile of i = P), so
- * lcsm_step / lcsm_run continue the generation.  When P is an FFT tile size
- * (above the direct crossover) the work is: copy the prompt into the state,
- * one 2P-point tile with the filter spectrum delayed by P rows (its outputs
- * are the causal convolution of the prompt), the same tile with the cached
+ * lcsm_init or lcsm_reset).  Afterwards the context is at position P, its
+ * pending accumulators hold the prompt's contributions from the gray tile of
+ * i = P, and lcsm_step / lcsm_run continue the generation as after P calls of
+ * lcsm_step.  When P is an FFT tile size (above the direct crossover) the work
+ * is one 2P-point tile with the filter spectrum delayed by P rows (its outputs
+ * are the causal convolution of the prompt) and the same tile with the cached
  * spectrum.  For a mirrored tile size both run on the mirror, the delayed
- * spectra made in the scratch; otherwise (or where one layer's do not fit
- * there) the spectra of tile size P are recomputed twice in place.  For a
- * direct tile size it runs the P ordinary steps.  Errors: LCSM_EINVAL (null
+ * spectra made in the scratch, and state rows < P are written only where a
+ * later tile reads them (no tile does while every larger size is mirrored);
+ * otherwise (or where one layer's spectra do not fit the scratch) the prompt
+ * is copied into state rows < P and the spectra of tile size P are recomputed
+ * twice in place.  For a direct tile size it runs the P ordinary steps.
+ * Errors: LCSM_EINVAL (null
  * pointers, P not a power of two, 2P > L, or 2P > T with half_state),
  * LCSM_ESTATE (not at position 0, or faulted), LCSM_EDEVICE. */
 int lcsm_prefill(lcsm_ctx* ctx, int P, const float* y, size_t y_stride, float* z, size_t z_stride);

@@ -55,8 +55,8 @@ struct Split {
 // the arguments instead of two), rows and the layer's pointers are uniform, so
 // that an address is a scalar base and the lane's 32-bit offset, and FULL (the
 // destination not clipped: every row and lag exists) needs no clamping.  Same
-// box, before and after: 8192 positions of 6144 columns 20.4 -> 19.9 ms, 65536 of
-// 18432 columns 209.2 -> 205.6, 32768 of 55296 columns 127.3 -> 125.7.
+// box, before and after: 8192 positions of 6144 columns 20.46 -> 19.91 ms, 65536 of
+// 18432 columns 207.9 -> 204.4, 32768 of 55296 columns 126.7 -> 125.2.
 template <int U, bool RED, bool FULL>
 __global__ __launch_bounds__(kThreads) void k_step_fused(const float* __restrict__ y,
                                                         float* __restrict__ z,
@@ -789,16 +789,13 @@ hipError_t launch_chain_block(const float* x, size_t xst, int xring, int xs0, fl
   if (s.M > kChainBlockMaxM || t1 <= t0 || (t0 & ~(kChainBlockW - 1)) != ((t1 - 1) & ~(kChainBlockW - 1)))
     return hipErrorInvalidValue;
   const int tl = tile_last ? 1 : 0;
+  static_assert(kChainLaneMaxM == 2, "one k_chain_lane per layer count");
 #define LCSM_CHAIN_LANE(ML)                                                                        \
   hipLaunchKernelGGL((k_chain_lane<ML>), dim3((unsigned)((s.BD + 63) / 64)), dim3(64), 0, st, x,   \
                      xst, xring, xs0, z, zst, zring, zs0, S, Hf, prev, s.L, s.SL, s.BD, s.D, t0, t1, \
                      tl)
-  if (s.M == 1) {
-    LCSM_CHAIN_LANE(1);
-    return hipGetLastError();
-  }
-  if (s.M == 2) {
-    LCSM_CHAIN_LANE(2);
+  if (s.M <= kChainLaneMaxM) {
+    if (s.M == 1) LCSM_CHAIN_LANE(1); else LCSM_CHAIN_LANE(2);
     return hipGetLastError();
   }
 #undef LCSM_CHAIN_LANE

@@ -65,13 +65,20 @@ hipError_t launch_chain_fused(const float* x, float* z, float* S, const float* H
 // lies inside one aligned block of kChainBlockW positions and whose gray
 // tiles are direct with U <= kChainBlockW / 2 (the last position's tile only
 // when tile_last).  Position t reads x slab (xs0 + t - t0) mod xring and
-// writes z slab (zs0 + t - t0) mod zring.  Full-state contexts with at most
-// kChainBlockMaxM layers; a workgroup takes up to kChainBlockCols columns of
-// every layer, and the launch is used while the columns fill at most
-// kChainBlockMaxGroups workgroups (one per compute unit: beyond that, the
-// serial chain of each workgroup makes one launch per position faster).
+// writes z slab (zs0 + t - t0) mod zring; no x slab may be the z slab of an
+// earlier position of the launch.  Full-state contexts with at most
+// kChainBlockMaxM layers; up to kChainLaneMaxM a lane takes one column of every
+// layer, above a workgroup up to kChainBlockCols columns.
+// The launch is used while the columns fill at most kChainBlockMaxGroups
+// workgroups of kChainBlockCols.  That line was drawn for the first form of the
+// block launch, one workgroup per compute unit; the present form stays ahead of
+// one launch per position above it as well (512 positions of 12 layers x 16384
+// columns 1.68 against 4.03 ms, of 65536 columns 7.10 against 9.08, of 30 layers
+// x 32768 10.7 against 12.7, of one layer x 16384 0.36 against 1.31), so it could
+// be drawn higher.
 constexpr int kChainBlockW = 32;
 constexpr int kChainBlockMaxM = 30;
+constexpr int kChainLaneMaxM = 2;
 constexpr int kChainXAhead = 4;  // positions by which the chained inputs are loaded ahead
 constexpr int kChainBlockCols = 32;
 constexpr int kChainBlockMaxGroups = 256;

@@ -60,10 +60,11 @@ __device__ __forceinline__ float gelu(float v) {
 // out rows r < nrows of the product W [N][K] x^T with x [nrows][K] (row
 // stride K): MODE kUp -> out[r][n] = gelu(sum + bias[n]) (row stride N);
 // MODE kDown -> a = sum + bias[n], out[r][n] = a (row stride N = D), then the
-// red cell of the next layer or the sampler copy.  nrows <= 4 RG; rows past
-// nrows and units past N are computed from the last one and not stored.  K
-// must be a multiple of 4.  W, and x of kUp and kDown alike, are in the quad
-// layout (quad_at); kUp writes out in it, kDown row by row.
+// red cell of the next layer or the sampler copy.  nrows <= 4 RG.  The rows past
+// nrows are those of the last quad, which init zeroes and nothing writes; units
+// past N are computed from the last quad of units; neither is stored.  K must be
+// a multiple of 4.  W, and x of kUp and kDown alike, are in the quad layout
+// (quad_at); kUp writes out in it, kDown row by row.
 //
 // A workgroup takes 4 UG output units; its waves split K into chunks of 64
 // (wave w: chunks w, w + nw, ...).  One v_mfma_f32_4x4x1_16b multiplies, in

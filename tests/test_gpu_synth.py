@@ -58,9 +58,9 @@ def _make(w, filters=None, weights=None, options=None):
                                    (2, 17, 8, 200), (1, 4, 64, 2048), (2, 9, 1500, 64)])
 def test_synth_matches_oracle(shape):
     """Includes the 16-channel 1024-position workload's shape, a ragged batch
-    (17 rows: two product launches of 16 and 1), every tile kind, and products
-    on the matrix cores with ragged blocks (9 of 16 rows; 3000 and 1500
-    units and inputs, neither a multiple of 16)."""
+    (17 rows: two product launches of 16 and 1), every tile kind, and 9 rows (a
+    last quad of one) against 3000 and 1500 units and inputs, whose last chunk of
+    64 is cut."""
     M, B, D, L = shape
     say(f"[synth] M={M} B={B} D={D} L={L}")
     w = datagen.Workload("synth", M, B, D, L, decay=L / 5, seed=50 + M + B)
