@@ -249,7 +249,7 @@ def kernel_key(name):
     """(kernel, U) of a library kernel name as the per-launch pass names it,
     or None for other kernels."""
     import re
-    m = re.search(r"k_step_fused<(\d+), (true|false)>", name)
+    m = re.search(r"k_step_fused<(\d+), (true|false)(?:, (?:true|false))?>", name)
     if m:
         u = int(m.group(1))
         if m.group(2) == "false":
@@ -484,7 +484,7 @@ def group_kernels(kind, U):
     is made of, as the per-launch pass groups them."""
     n = 2 * U
     if kind in ("fused", "red"):
-        return lambda k: k == f"k_step_fused<{U}, true>"
+        return lambda k: k.startswith((f"k_step_fused<{U}, true>", f"k_step_fused<{U}, true, "))
     if kind == "direct":
         return lambda k: k.startswith("k_direct_tile")
     if kind == "fft_lds":

@@ -291,7 +291,7 @@ __global__ __launch_bounds__(kThreads) void k_chain_fused(const float* __restric
 // that does not need the newest input follow in the phase after, and x is
 // loaded kChainXAhead positions ahead.  18 layers x 3072 columns: 49.5 us per
 // 32 positions when each position's layer work ran between the chain's end
-// and its next start, 27.8 with the phases.
+// and its next start, 28.7 with the phases.
 // f(std::integral_constant<int, 0>{}), ..., f(std::integral_constant<int, N-1>{}).
 template <class F, int... R>
 __device__ __forceinline__ void static_for_impl(F& f, std::integer_sequence<int, R...>) {

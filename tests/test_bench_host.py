@@ -19,6 +19,9 @@ ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
     ("lcsm::k_step_fused<32, true>", ("fused", 32)),
     ("lcsm::k_step_fused<0, true>", ("red", 0)),
     ("lcsm::k_step_fused<8, false>", ("direct", 8)),
+    ("void lcsm::(anonymous namespace)::k_step_fused<1, true, true>(float const*, float*)", ("fused", 1)),
+    ("lcsm::k_step_fused<0, true, true>", ("red", 0)),
+    ("lcsm::k_step_fused<16, false, false>", ("direct", 16)),
     ("lcsm::k_fft_tile<8192, false, true, false>", ("fft_lds", 4096)),
     ("lcsm::k_fft_tile<4096, true, true, false, 4>", ("fft_lds", 2048)),
     ("lcsm::k_fft_tile<128, true, false, false, 8>(float*, float2 const*)", ("fft_lds", 64)),
@@ -154,6 +157,7 @@ def test_group_kernels_picks_the_dispatches_of_one_launch():
     assert g("k_fft_tile<1024, true, true, false, 8>") and not g("k_fft_tile<128, true, true, false, 8>")
     g = bench.group_kernels("fused", 1)
     assert g("k_step_fused<1, true>") and not g("k_step_fused<16, true>")
+    assert g("k_step_fused<1, true, false>") and not g("k_step_fused<1, false, true>")
     g = bench.group_kernels("fft_hbm", 32768)
     assert g("k_fft_rows_fwd<1024, false>") and g("k_fft_mid_tile<16>") and not g("k_cm_yin4")
 

@@ -69,3 +69,22 @@ def test_row_panel_tile_keeps_two_workgroups(vgprs, N):
     got = [v for n, v in vgprs.items() if f"k_fft_tileILi{N}ELb0E" in n or f"k_fft_tileILi{N}ELb1E" in n]
     assert len(got) >= 4
     assert max(got) <= 128
+
+
+def test_profile_grouping_knows_every_step_and_tile_kernel(vgprs):
+    """The profile summaries group dispatches by kernel name: every kernel that a
+    teacher-forced generation launches is one of their keys, and every step form
+    is among the dispatches of its launch."""
+    import bench
+    if not shutil.which("c++filt"):
+        pytest.skip("c++filt is not installed")
+    names = subprocess.run(["c++filt", *vgprs], check=True, capture_output=True, text=True).stdout.split("\n")
+    short = [bench.short_name(n) for n in names if n]
+    path = ("k_step_fused", "k_fft_tile", "k_fft_coltile", "k_cm_", "k_rows_to_cols", "k_cols_to_rows",
+            "k_fft_rows_inv", "k_fft_rows_fwd", "k_fft_mid_tile")
+    timed = [n for n in short if n.startswith(path)]
+    assert len(timed) > 50
+    assert [n for n in timed if bench.kernel_key(n) is None] == []
+    for U in (1, 2, 4, 8, 16, 32, 64):
+        keep = bench.group_kernels("fused", U)
+        assert len([n for n in timed if keep(n)]) == 2  # destination whole and clipped
